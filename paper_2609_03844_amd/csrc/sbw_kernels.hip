@@ -18,8 +18,9 @@
 // candidates  the watermark restricted to caller-given candidate ids per row (the
 //             top-k self-salt scheme): one workgroup per row.
 // green_mask  one lane per 32-token word of the bit set.
-// detect      one wavefront per sequence; each lane scores positions i, i+64, ...
-//             and the wave counts green positions with a ballot + popcount.  With
+// detect      one wavefront per sequence, or up to 16 wavefronts and several workgroups
+//             for few sequences; each lane scores positions i, i+64, ... and a wave
+//             counts green positions with a ballot + popcount.  With
 //             repeated n-grams scored once: one workgroup per sequence and an LDS
 //             hash set of first occurrences.
 //
@@ -1374,6 +1375,7 @@ green_mask_kernel(uint32_t* __restrict__ bits, uint32_t V, uint32_t words_per_ro
 // ---------------------------------------------------------------------------
 constexpr int kWave = 64;
 constexpr int kWavesPerBlock = kThreads / kWave;
+constexpr int kMaxSplitWaves = 16;   // most waves of a workgroup that share a sequence
 
 // Lane `l`'s 64-bit value, in every lane.
 __device__ __forceinline__ uint64_t readlane64(uint64_t x, int l) {
@@ -1423,8 +1425,8 @@ __device__ __forceinline__ bool window_green(uint64_t key, const uint32_t (&w)[k
 }
 
 // Positions handled per lane per pass: a pass covers 64 * kChunk positions and
-// issues all of its token loads before any arithmetic.  The host picks kChunk from
-// the number of scored positions so that short sequences do not compute idle slots.
+// issues all of its token loads before any arithmetic.  The host picks kChunk (see
+// detect_plan).
 // Outputs of a detect launch; `lengths` (per-sequence token counts, clamped to
 // [0, L]) and `scored` (T per sequence) may be null.
 struct DetectIO {
@@ -1447,21 +1449,135 @@ __device__ __forceinline__ void detect_store(const DetectIO& io, int64_t n, uint
   const double denominator = sqrt(t * gamma * (1.0 - gamma));
   io.counts[n] = static_cast<int32_t>(green);
   if (io.scored != nullptr) io.scored[n] = static_cast<int32_t>(T);
-  io.z[n] = numerator / denominator;
+  // atomic, as detect_split_kernel's adds into the same slot are
+  __hip_atomic_store(&io.z[n], numerator / denominator, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Positions are 32-bit (L < 2^31).  Lanes past the end of the sequence load the last
-// token instead (a valid address), so the loads need no branch; their positions are
-// masked out of the count with a lane mask built in scalar registers.  The four waves
-// of a workgroup take four sequences; their counts meet in LDS and one wave computes
-// the four z-scores side by side (lanes 0-3), so the fp64 epilogue issues once per
-// workgroup instead of once per wave.  Every wave of the workgroup runs the same
-// number of outer iterations, so the barriers are reached by all of them.
+// One wave's pass: the green positions among base .. base + 64 * kChunk - 1 of a sequence
+// of `len` tokens (wave-uniform result; base < len).  Positions are 32-bit (L < 2^31).
+// Lanes past the end of the sequence load the last token instead (a valid address), so
+// the loads need no branch; their positions are masked out of the count with a lane mask
+// built in scalar registers.
+//
+// Self-salt with a window of several tokens needs K J(w) of every window token: each lane
+// computes it once for its own token and the wave shares the products through `kj_lds`
+// (kPassTerms entries of its own): position i reads the entries of i - width .. i - 1.
+template <int kSeeding, int kW>
+constexpr bool kWindowTerms = kSeeding == kSelfSalt && kW > 1;
+template <int kChunk>
+constexpr int kPassTerms = kMaxWidth + kWave * kChunk;   // the window before the pass, then its tokens
+
+template <int kSeeding, int kChunk, int kW>
+__device__ __forceinline__ uint32_t detect_pass(const int32_t* seq, uint32_t base, uint32_t len, int width,
+                                                uint64_t key, uint32_t tm1, uint32_t lane,
+                                                uint64_t* kj_lds) {
+  // The pass's tokens and their windows from two wave-uniform bases; each load adds the
+  // lane's byte offset, clamped to the pass's last position.
+  const char* pass = reinterpret_cast<const char*>(seq + base);
+  const char* pass_w = pass - 4 * width;
+  const uint32_t rem = len - base;              // positions left, > 0
+  const uint32_t last_byte = 4u * (min(rem, static_cast<uint32_t>(kWave * kChunk)) - 1u);
+  uint32_t w[kChunk][kW], v[kChunk];
+#pragma unroll
+  for (int c = 0; c < kChunk; ++c) {
+    const uint32_t ob = min(4u * (static_cast<uint32_t>(c * kWave) + lane), last_byte);
+    v[c] = *reinterpret_cast<const uint32_t*>(pass + ob);
+#pragma unroll
+    for (int k = 0; k < kW; ++k)
+      w[c][k] = ((kW == 1 || k < width) && kSeeding == kContext)
+                    ? *reinterpret_cast<const uint32_t*>(pass_w + ob + 4u * static_cast<uint32_t>(k))
+                    : 0u;
+  }
+  // Independent membership chains first (instruction-level parallelism), then one ballot
+  // per chunk.
+  bool g[kChunk];
+  if constexpr (kWindowTerms<kSeeding, kW>) {
+    uint32_t before = 0u;   // lanes 0 .. width - 1: the window of the pass's first position
+    if (lane < static_cast<uint32_t>(width)) before = *reinterpret_cast<const uint32_t*>(pass_w + 4u * lane);
+    uint32_t jv[kChunk];
+    uint64_t kj[kChunk];
+    uint64_t* mine = kj_lds + kMaxWidth + lane;
+#pragma unroll
+    for (int c = 0; c < kChunk; ++c) {
+      jv[c] = jenkins32_lane(v[c]);
+      kj[c] = lane_mul_64x32(key, jv[c]);
+      mine[c * kWave] = kj[c];
+    }
+    if (lane < static_cast<uint32_t>(width))
+      mine[-width] = lane_mul_64x32(key, jenkins32_lane(before));
+    // LDS operations of one wave complete in order; the fences keep the compiler from
+    // moving the reads above the writes, or the next pass's writes above these reads.
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    const uint64_t* win = mine - width;
+#pragma unroll
+    for (int c = 0; c < kChunk; ++c) {
+      uint64_t r = lane_mul_64x32(kj[c], jv[c]);
+#pragma unroll
+      for (int k = 0; k < kW; ++k) {
+        if (k < width) {
+          const uint64_t t = lane_mul_64x32(win[c * kWave + k], jv[c]);
+          r = t < r ? t : r;
+        }
+      }
+      g[c] = is_green(cbrng_lane(v[c], r), tm1);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  } else if constexpr (kSeeding == kSelfSalt) {
+    // Self-salt, width 1: the seed of position i is min(K J(p) J(v), K J(v) J(v)) with p
+    // the token at i - 1.  Each lane computes K J(v) of its own token once; position i's
+    // K J(p) is position i - 1's K J(v), held by the lane before (lane 63 of the chunk
+    // before, for lane 0), and a wave shift hands it over.  The pass's first window token
+    // is the same for the whole wave: one scalar load, hashed in scalar registers.
+    uint32_t jv[kChunk];
+    uint64_t kj[kChunk];
+#pragma unroll
+    for (int c = 0; c < kChunk; ++c) {
+      jv[c] = jenkins32_lane(v[c]);
+      kj[c] = lane_mul_64x32(key, jv[c]);
+    }
+    const uint32_t p0 = *reinterpret_cast<const uint32_t*>(pass_w);
+    uint64_t carry = key * static_cast<uint64_t>(jenkins32(p0));
+#pragma unroll
+    for (int c = 0; c < kChunk; ++c) {
+      if (c > 0) carry = readlane64(kj[c - 1], kWave - 1);
+      const uint64_t kjp = wave_shift_right(kj[c], carry);
+      const uint64_t self = lane_mul_64x32(kj[c], jv[c]);
+      const uint64_t t = lane_mul_64x32(kjp, jv[c]);
+      g[c] = is_green(cbrng_lane(v[c], t < self ? t : self), tm1);
+    }
+  } else {
+#pragma unroll
+    for (int c = 0; c < kChunk; ++c) g[c] = window_green<kSeeding, kW>(key, w[c], width, v[c], tm1);
+  }
+  // Chunks before rem / 64 lie inside the sequence, the next one holds its last rem % 64
+  // positions, the others none (masks in scalar registers).
+  const uint32_t full_chunks = rem / static_cast<uint32_t>(kWave);
+  const uint64_t part_mask = (uint64_t{1} << (rem % static_cast<uint32_t>(kWave))) - 1u;
+  uint32_t green = 0u;
+#pragma unroll
+  for (int c = 0; c < kChunk; ++c) {
+    const uint32_t cu = static_cast<uint32_t>(c);
+    const uint64_t valid = cu < full_chunks ? ~uint64_t{0} : (cu == full_chunks ? part_mask : 0u);
+    green += static_cast<uint32_t>(__popcll(__ballot(g[c]) & valid));
+  }
+  return green;
+}
+
+// Many sequences: one wave each.  The four waves of a workgroup take four sequences;
+// their counts meet in LDS and one wave computes the four z-scores side by side (lanes
+// 0-3), so the fp64 epilogue issues once per workgroup instead of once per wave.  Every
+// wave of the workgroup runs the same number of outer iterations, so the barriers are
+// reached by all of them.
 template <int kSeeding, int kChunk, int kW>
 __global__ void __launch_bounds__(kThreads)
 detect_kernel(const int32_t* __restrict__ tokens, int64_t N, int64_t L, int64_t row_stride,
               int width, uint64_t key, uint32_t tm1, double gamma, DetectIO io) {
   __shared__ uint32_t lds_green[kWavesPerBlock], lds_len[kWavesPerBlock];
+  __shared__ uint64_t lds_terms[kWindowTerms<kSeeding, kW> ? kWavesPerBlock * kPassTerms<kChunk> : 1];
   const uint32_t lane = threadIdx.x % kWave;
   // the wave's index in the workgroup, in a scalar register
   const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x / kWave));
@@ -1473,67 +1589,9 @@ detect_kernel(const int32_t* __restrict__ tokens, int64_t N, int64_t L, int64_t 
     if (n < N) {
       const int32_t* seq = tokens + n * row_stride;
       len = static_cast<uint32_t>(sequence_length(io.lengths, n, L));
-      for (uint32_t base = static_cast<uint32_t>(width); base < len; base += kWave * kChunk) {
-        // The pass's tokens and their windows from two wave-uniform bases; each load
-        // adds the lane's byte offset, clamped to the pass's last position.
-        const char* pass = reinterpret_cast<const char*>(seq + base);
-        const char* pass_w = pass - 4 * width;
-        const uint32_t rem = len - base;              // positions left, > 0
-        const uint32_t last_byte = 4u * (rem - 1u);
-        uint32_t w[kChunk][kW], v[kChunk];
-        constexpr bool kShared = kSeeding == kSelfSalt && kW == 1;   // terms handed over
-#pragma unroll
-        for (int c = 0; c < kChunk; ++c) {
-          const uint32_t ob = min(4u * (static_cast<uint32_t>(c * kWave) + lane), last_byte);
-          v[c] = *reinterpret_cast<const uint32_t*>(pass + ob);
-#pragma unroll
-          for (int k = 0; k < kW; ++k)
-            w[c][k] = ((kW == 1 || k < width) && !kShared)
-                          ? *reinterpret_cast<const uint32_t*>(pass_w + ob + 4u * static_cast<uint32_t>(k))
-                          : 0u;
-        }
-        // Independent membership chains first (instruction-level parallelism), then
-        // one ballot per chunk.
-        bool g[kChunk];
-        if constexpr (kShared) {
-          // Self-salt, width 1: the seed of position i is min(K J(p) J(v), K J(v) J(v))
-          // with p the token at i - 1.  Each lane computes K J(v) of its own token once;
-          // position i's K J(p) is position i - 1's K J(v), held by the lane before (lane
-          // 63 of the chunk before, for lane 0), and a wave shift hands it over.  The
-          // pass's first window token is the same for the whole wave: one scalar load,
-          // hashed in scalar registers.
-          uint32_t jv[kChunk];
-          uint64_t kj[kChunk];
-#pragma unroll
-          for (int c = 0; c < kChunk; ++c) {
-            jv[c] = jenkins32_lane(v[c]);
-            kj[c] = lane_mul_64x32(key, jv[c]);
-          }
-          const uint32_t p0 = *reinterpret_cast<const uint32_t*>(pass_w);
-          uint64_t carry = key * static_cast<uint64_t>(jenkins32(p0));
-#pragma unroll
-          for (int c = 0; c < kChunk; ++c) {
-            if (c > 0) carry = readlane64(kj[c - 1], kWave - 1);
-            const uint64_t kjp = wave_shift_right(kj[c], carry);
-            const uint64_t self = lane_mul_64x32(kj[c], jv[c]);
-            const uint64_t t = lane_mul_64x32(kjp, jv[c]);
-            g[c] = is_green(cbrng_lane(v[c], t < self ? t : self), tm1);
-          }
-        } else {
-#pragma unroll
-          for (int c = 0; c < kChunk; ++c) g[c] = window_green<kSeeding, kW>(key, w[c], width, v[c], tm1);
-        }
-        // Chunks before rem / 64 lie inside the sequence, the next one holds its last
-        // rem % 64 positions, the others none (masks in scalar registers).
-        const uint32_t full_chunks = rem / static_cast<uint32_t>(kWave);
-        const uint64_t part_mask = (uint64_t{1} << (rem % static_cast<uint32_t>(kWave))) - 1u;
-#pragma unroll
-        for (int c = 0; c < kChunk; ++c) {
-          const uint32_t cu = static_cast<uint32_t>(c);
-          const uint64_t valid = cu < full_chunks ? ~uint64_t{0} : (cu == full_chunks ? part_mask : 0u);
-          green += static_cast<uint32_t>(__popcll(__ballot(g[c]) & valid));
-        }
-      }
+      for (uint32_t base = static_cast<uint32_t>(width); base < len; base += kWave * kChunk)
+        green += detect_pass<kSeeding, kChunk, kW>(seq, base, len, width, key, tm1, lane,
+                                                   lds_terms + wave * kPassTerms<kChunk>);
     }
     if (lane == 0u) {
       lds_green[wave] = green;
@@ -1546,6 +1604,55 @@ detect_kernel(const int32_t* __restrict__ tokens, int64_t N, int64_t L, int64_t 
     }
     __syncthreads();  // the LDS slots are rewritten by the next iteration
   }
+}
+
+// Few sequences: the waves of a workgroup (2-16) share one sequence, and `splits`
+// workgroups share it too where a sequence is long.  Unit u of the sequence's
+// units = splits * waves takes the passes u, u + units, ... of 64 * kChunk positions, so
+// texts of any length spread evenly.  With one split the workgroup stores the result.
+// With more, the partial counts meet in the sequence's z slot, zeroed by
+// detect_zero_kernel before: one 64-bit add carries an arrival (high word) and the green
+// count (low word), so the add that brings the last arrival returns all the others'
+// counts with it and no fence is needed; that workgroup stores the result over the slot.
+template <int kSeeding, int kChunk, int kW>
+__global__ void __launch_bounds__(kWave * kMaxSplitWaves)
+detect_split_kernel(const int32_t* __restrict__ tokens, int64_t L, int64_t row_stride, int width,
+                    uint64_t key, uint32_t tm1, double gamma, uint32_t splits, DetectIO io) {
+  __shared__ uint32_t lds_green[kMaxSplitWaves];
+  __shared__ uint64_t lds_terms[kWindowTerms<kSeeding, kW> ? kMaxSplitWaves * kPassTerms<kChunk> : 1];
+  const uint32_t lane = threadIdx.x % kWave;
+  const uint32_t wave =
+      static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x / kWave)));
+  const uint32_t waves = blockDim.x / kWave;
+  const uint32_t n = blockIdx.x / splits;
+  const uint32_t split = blockIdx.x % splits;
+  const int32_t* seq = tokens + static_cast<int64_t>(n) * row_stride;
+  const uint32_t len = static_cast<uint32_t>(sequence_length(io.lengths, n, L));
+  constexpr uint32_t kPass = kWave * kChunk;
+  const uint32_t step = splits * waves * kPass;
+  uint32_t green = 0u;  // wave-uniform count
+  for (uint32_t base = static_cast<uint32_t>(width) + (split * waves + wave) * kPass; base < len; base += step)
+    green += detect_pass<kSeeding, kChunk, kW>(seq, base, len, width, key, tm1, lane,
+                                               lds_terms + wave * kPassTerms<kChunk>);
+  if (lane == 0u) lds_green[wave] = green;
+  __syncthreads();
+  if (threadIdx.x != 0u) return;
+  uint32_t sum = 0u;
+  for (uint32_t w = 0; w < waves; ++w) sum += lds_green[w];
+  if (splits > 1u) {
+    uint64_t* slot = reinterpret_cast<uint64_t*>(io.z) + n;
+    const uint64_t before = __hip_atomic_fetch_add(slot, (uint64_t{1} << 32) | sum, __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_AGENT);
+    if (static_cast<uint32_t>(before >> 32) != splits - 1u) return;
+    sum += static_cast<uint32_t>(before);
+  }
+  detect_store(io, n, sum, len > static_cast<uint32_t>(width) ? len - width : 0, gamma);
+}
+
+// Zeroes the z slots that detect_split_kernel adds into.
+__global__ void __launch_bounds__(kThreads) detect_zero_kernel(uint64_t* __restrict__ slots, int64_t N) {
+  const int64_t n = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x;
+  if (n < N) slots[n] = 0u;
 }
 
 // Detection with each distinct (width+1)-gram scored once.  One workgroup per
@@ -1917,23 +2024,84 @@ void dispatch_argmax(const void* logits, int64_t B, uint32_t V, int64_t row_stri
                                                     values, partials, st);
 }
 
+// How a detect launch spreads over the chip: waves and workgroups per sequence, positions
+// per lane and pass.  All times per launch, 100-launch graphs, one box (start = one wave
+// per sequence, 8 chunks a pass).
+//  * A wave per sequence (detect_kernel) where the sequences alone fill the chip: above
+//    1024 of them with a window of one token (N = 2048, L = 512, context: 4.3 us against
+//    4.8 with 4 waves), above 2048 with wider windows (N = 2048, L = 512 / 1024, width 4:
+//    context 5.5 / 7.8 us with 4 waves against 7.0 / 11.2).  Chunks per pass: the most that
+//    pad a sequence by at most an eighth (N = 16384, L = 300, self-salt: 15.2 us with one
+//    chunk, 20.8 with 8; N = 4096, L = 512: 7.7 against 7.1 the other way).
+//  * Below, up to 16 waves share a sequence, as many as keep 8192 waves in all and one
+//    chunk each (two each from 512 sequences: N = 1024, L = 512, self-salt 4.1 us, one each
+//    4.4); two chunks a pass where a wave has them.  N = 128, L = 2048, self-salt width 4:
+//    19.6 -> 4.5 us.
+//  * Longer than 64 chunks, 8-wave workgroups split a sequence, splits^2 * N <= 2048:
+//    more splits cost more in adds to one slot than they save, and the zeroing launch
+//    costs about 2 us (N = 32, L = 4096: 5.1 us unsplit, 5.4 split; L = 16384: 122 -> 7.0).
+//    N = 8, L = 16384, context width 4: 121 us at the start, 6.1 now.
+//  * Context seeding with a wide window takes one chunk a pass throughout: the window's
+//    loads of several chunks in flight cost more than they hide (N = 4096, L = 512,
+//    width 4: 7.8 us, with 8 chunks 9.2).
+struct DetectPlan {
+  int waves, chunk;
+  uint32_t splits;   // 0: detect_kernel, one wave per sequence
+};
+
+template <int kSeeding, int kW>
+constexpr int kMaxDetectChunk = kSeeding == kContext && kW > 1 ? 1 : (kW > kMidWidth ? 4 : 8);
+
+template <int kSeeding, int kW>
+DetectPlan detect_plan(int64_t N, int64_t positions) {
+  constexpr int kMaxChunk = kMaxDetectChunk<kSeeding, kW>;
+  const int64_t chunks = (positions + kWave - 1) / kWave;
+  if (N > (kW == 1 ? 1024 : 2048) || chunks < 2) {
+    int chunk = kMaxChunk;
+    while (chunk > 1 && ((chunks + chunk - 1) / chunk * chunk - chunks) * 8 > chunks) chunk /= 2;
+    return DetectPlan{1, chunk, 0u};
+  }
+  DetectPlan p{kMaxSplitWaves, 1, 1u};
+  if (chunks > 64) {
+    while (p.splits * 16 <= chunks && 4 * int64_t{p.splits} * p.splits * N <= 2048) p.splits *= 2;
+    if (p.splits > 1u) p.waves = 8;
+  }
+  const int64_t each = kMaxChunk > 1 && N >= 512 ? 2 : 1;   // chunks that a wave has at least
+  while (p.waves > 1 && (p.waves * N > 8192 || p.waves * each > chunks)) p.waves /= 2;
+  if (kMaxChunk > 1 && 2 * p.waves * int64_t{p.splits} <= chunks) p.chunk = 2;
+  return p;
+}
+
 template <int kSeeding, int kW>
 void launch_detect(int64_t positions, hipStream_t st, const int32_t* tokens, int64_t N, int64_t L,
                    int64_t row_stride, int width, uint64_t key, uint32_t tm1, double gamma,
                    const DetectIO& io) {
-  const int64_t blocks = grid_for((N + kWavesPerBlock - 1) / kWavesPerBlock);
-  if (positions <= kWave)
-    hipLaunchKernelGGL((detect_kernel<kSeeding, 1, kW>), dim3(blocks), dim3(kThreads), 0, st,
-                       tokens, N, L, row_stride, width, key, tm1, gamma, io);
-  else if (positions <= 2 * kWave)
-    hipLaunchKernelGGL((detect_kernel<kSeeding, 2, kW>), dim3(blocks), dim3(kThreads), 0, st,
-                       tokens, N, L, row_stride, width, key, tm1, gamma, io);
-  else if (positions <= 4 * kWave || kW > kMidWidth)   // windows of 5-8: 4 chunks (registers)
-    hipLaunchKernelGGL((detect_kernel<kSeeding, 4, kW>), dim3(blocks), dim3(kThreads), 0, st,
-                       tokens, N, L, row_stride, width, key, tm1, gamma, io);
-  else
-    hipLaunchKernelGGL((detect_kernel<kSeeding, 8, kW>), dim3(blocks), dim3(kThreads), 0, st,
-                       tokens, N, L, row_stride, width, key, tm1, gamma, io);
+  constexpr int kMaxChunk = kMaxDetectChunk<kSeeding, kW>;
+  const DetectPlan plan = detect_plan<kSeeding, kW>(N, positions);
+  if (plan.splits == 0u) {
+    const dim3 grid(static_cast<uint32_t>(grid_for((N + kWavesPerBlock - 1) / kWavesPerBlock)));
+    auto launch = [&](auto chunk) {
+      constexpr int kChunk = decltype(chunk)::value <= kMaxChunk ? decltype(chunk)::value : kMaxChunk;
+      hipLaunchKernelGGL((detect_kernel<kSeeding, kChunk, kW>), grid, dim3(kThreads), 0, st, tokens, N,
+                         L, row_stride, width, key, tm1, gamma, io);
+    };
+    if (plan.chunk == 1) launch(std::integral_constant<int, 1>{});
+    else if (plan.chunk == 2) launch(std::integral_constant<int, 2>{});
+    else if (plan.chunk == 4) launch(std::integral_constant<int, 4>{});
+    else launch(std::integral_constant<int, 8>{});
+    return;
+  }
+  if (plan.splits > 1u)
+    hipLaunchKernelGGL(detect_zero_kernel, dim3(static_cast<uint32_t>((N + kThreads - 1) / kThreads)),
+                       dim3(kThreads), 0, st, reinterpret_cast<uint64_t*>(io.z), N);
+  auto launch = [&](auto chunk) {
+    constexpr int kChunk = decltype(chunk)::value <= kMaxChunk ? decltype(chunk)::value : kMaxChunk;
+    hipLaunchKernelGGL((detect_split_kernel<kSeeding, kChunk, kW>),
+                       dim3(static_cast<uint32_t>(N) * plan.splits), dim3(kWave * plan.waves), 0, st,
+                       tokens, L, row_stride, width, key, tm1, gamma, plan.splits, io);
+  };
+  if (plan.chunk == 1) launch(std::integral_constant<int, 1>{});
+  else launch(std::integral_constant<int, 2>{});
 }
 
 template <int kSeeding, int kW>
