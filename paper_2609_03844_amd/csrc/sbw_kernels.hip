@@ -1,14 +1,14 @@
 // HIP kernels and C ABI of libsbw (declared in include/sbw.h) for MI355X / gfx950.
 //
 // watermark   one streaming pass over the logits: each lane owns 16-byte vectors
-//             of a row (4 fp32 or 8 bf16 logits), loads them, derives the green
-//             decision in registers (seed, Philox4x32-10 draw, threshold compare)
-//             and stores them back.  Row-uniform values (the window of previous
+//             of a row (4 fp32 or 8 bf16 logits; self-salt 4 of either), loads them,
+//             derives the green decision in registers (seed, Philox4x32-10 draw, threshold
+//             compare) and stores them back.  Row-uniform values (the window of previous
 //             tokens, the context seed, key * J(p_i)) sit in scalar registers.
 //             Context seeding shares one Philox block between the 4 tokens of a
-//             counter; self-salt needs one block per token, and its workgroups
-//             share each candidate's hash and self term across up to 4 rows.  Large
-//             self-salt launches (window of one token) instead draw each
+//             counter; self-salt needs one block per token, and its workgroups take
+//             several rows in turn with each candidate's hash and self term computed
+//             once.  Large self-salt launches (window of one token) instead draw each
 //             column's self-term block once per slab of 12, 8 or 6 rows and queue in
 //             LDS only the pairs whose row term is the smaller one (about half).
 // argmax      greedy decoding of the watermarked logits without writing them: one
@@ -47,38 +47,15 @@ namespace {
 #ifndef SBW_CONTEXT_UNROLL_BF16
 #define SBW_CONTEXT_UNROLL_BF16 2
 #endif
-#ifndef SBW_SELF_SALT_UNROLL
-#define SBW_SELF_SALT_UNROLL 2 // 16-byte vectors per lane, self-salt fp32 (Philox-bound)
-#endif
-#ifndef SBW_SELF_SALT_UNROLL_BF16
-#define SBW_SELF_SALT_UNROLL_BF16 1
-#endif
-// Self-salt rows per workgroup (sharing the candidate terms) are chosen per launch,
-// for width 1 only (with a wider window the window terms dominate and sharing does
-// not pay): the most rows, up to 4 for fp32 and 2 for bf16 (register pressure), that
-// still leave SBW_SELF_SALT_MIN_GROUPS workgroups.
-// A self-salt workgroup may also take several row groups (at most ..._GROUP_ITERS,
-// while SBW_SELF_SALT_MIN_GROUPS workgroups remain), computing the candidate terms
-// once, and load the next group while drawing the current one (..._PREFETCH).
-#ifndef SBW_SELF_SALT_GROUP_ITERS
-#define SBW_SELF_SALT_GROUP_ITERS 1
-#endif
-#ifndef SBW_SELF_SALT_PREFETCH
-#define SBW_SELF_SALT_PREFETCH 0
-#endif
-#ifndef SBW_SELF_SALT_GROUP_ITERS_BF16
-#define SBW_SELF_SALT_GROUP_ITERS_BF16 4
-#endif
-#ifndef SBW_SELF_SALT_PREFETCH_BF16
-#define SBW_SELF_SALT_PREFETCH_BF16 1
-#endif
-// Self-salt, width 1 (fp32 and bf16): the split-term slab kernel with 12-row slabs when
-// that makes at least SBW_SLAB12_MIN_GROUPS workgroups, else with 8-row, else with 6-row
-// slabs when that makes at least SBW_SLAB_MIN_GROUPS (below that its long-lived waves
-// leave the chip underfilled and the row-group kernel is faster).  12-row slabs need
-// more workgroups than the others: with fewer than ~1.7 rounds of the ~1800 that fit
-// at once, the last round's tail costs more than the shorter slabs' extra self terms.
-// 0 = off.
+// Self-salt, width 1: the split-term slab kernel.  fp32: 12-row slabs when that makes at
+// least SBW_SLAB12_MIN_GROUPS workgroups, else with 8-row, else with 6-row slabs when that
+// makes at least SBW_SLAB_MIN_GROUPS (below that its long-lived waves leave the chip
+// underfilled and the row kernel is faster).  12-row slabs need more workgroups than the
+// others: with fewer than ~1.7 rounds of the ~1800 that fit at once, the last round's tail
+// costs more than the shorter slabs' extra self terms.  bf16: 12-row slabs from
+// SBW_SLAB_BF16_MIN_GROUPS, B = 1024 of 152064 (6450 workgroups: 215 us, row kernel 228);
+// below the row kernel is at least as fast (B = 512, 3225: 116.1 / 115.7; B = 256:
+// 62.5 / 59.1; B = 128 of 128256: 32.0 / 27.7).  SBW_SELF_SALT_SLAB 0 = off.
 #ifndef SBW_SELF_SALT_SLAB
 #define SBW_SELF_SALT_SLAB 1
 #endif
@@ -95,11 +72,11 @@ namespace {
 #ifndef SBW_SLAB_MIN_GROUPS
 #define SBW_SLAB_MIN_GROUPS 2000
 #endif
+#ifndef SBW_SLAB_BF16_MIN_GROUPS
+#define SBW_SLAB_BF16_MIN_GROUPS 4800
+#endif
 #ifndef SBW_SLAB12_MIN_GROUPS
 #define SBW_SLAB12_MIN_GROUPS 3000
-#endif
-#ifndef SBW_SELF_SALT_MIN_GROUPS
-#define SBW_SELF_SALT_MIN_GROUPS 1024  // 2048 measured 5 % slower for B * V of 5-10 M logits
 #endif
 
 constexpr int kThreads = 256;            // 4 wavefronts of 64
@@ -112,11 +89,69 @@ constexpr int64_t kMaxGridY = 65535;
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-template <typename V>
-__device__ __forceinline__ V stream_load(const V* p) { return __builtin_nontemporal_load(p); }
-template <typename V>
-__device__ __forceinline__ void stream_store(V* p, V v) { __builtin_nontemporal_store(v, p); }
+// A 16-byte vector of logits: 4 fp32 (as values) or 8 bf16 (as packed bits), and the same
+// in memory, where it is aligned to one logit only: a row may start anywhere (an odd
+// vocabulary, a slice of a padded buffer).  gfx950 takes 16-byte global accesses at any
+// byte address, so both give the same instruction; what an odd address costs is a ninth
+// 128-byte line for every 1 KB a wave moves.  Context pass, 256 rows of 152064 / 152065
+// columns: fp32 48.1 / 51.9 us, bf16 26.2 / 27.4 us; the element-wise kernel that such
+// rows took before: 117.7 and 102.9 us.
+typedef f32x4 f32x4_memory __attribute__((aligned(4)));
+typedef u32x4 u32x4_memory __attribute__((aligned(2)));
+template <typename T>
+struct VecOf {
+  typedef f32x4 Value;
+  typedef f32x4_memory Memory;
+};
+template <>
+struct VecOf<uint16_t> {
+  typedef u32x4 Value;
+  typedef u32x4_memory Memory;
+};
 
+// The 4 tokens of one Philox counter: 16 bytes of fp32 logits, 8 of bf16.
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef u32x2 u32x2_memory __attribute__((aligned(2)));
+template <typename T>
+struct QuadOf {
+  typedef f32x4 Value;
+  typedef f32x4_memory Memory;
+};
+template <>
+struct QuadOf<uint16_t> {
+  typedef u32x2 Value;
+  typedef u32x2_memory Memory;
+};
+
+// Overloads, not a template: a template argument would lose the alignment.
+__device__ __forceinline__ f32x4 stream_load(const f32x4_memory* p) { return __builtin_nontemporal_load(p); }
+__device__ __forceinline__ u32x4 stream_load(const u32x4_memory* p) { return __builtin_nontemporal_load(p); }
+__device__ __forceinline__ void stream_store(f32x4_memory* p, f32x4 v) { __builtin_nontemporal_store(v, p); }
+__device__ __forceinline__ void stream_store(u32x4_memory* p, u32x4 v) { __builtin_nontemporal_store(v, p); }
+
+__device__ __forceinline__ u32x2 stream_load(const u32x2_memory* p) { return __builtin_nontemporal_load(p); }
+__device__ __forceinline__ void stream_store(u32x2_memory* p, u32x2 v) { __builtin_nontemporal_store(v, p); }
+
+// How a row of V columns with token ids from vbase falls into 16-byte vectors whose first
+// token id is a multiple of their kPer tokens (so that they hold whole Philox blocks):
+// `head` columns before the first vector (0-3 fp32, 0-7 bf16; 0 unless the row is a shard
+// starting at an odd id), `full` vectors, `tail` columns after the last.
+struct RowSplit {
+  uint32_t head, full, tail;
+  uint32_t id;   // the first vector's token id / kPer
+  __device__ __forceinline__ uint32_t edges() const { return head + tail; }
+  // the column of edge e, 0 <= e < edges()
+  template <uint32_t kPer>
+  __device__ __forceinline__ uint32_t edge(uint32_t e) const {
+    return e < head ? e : full * kPer + e;
+  }
+};
+template <uint32_t kPer>
+__host__ __device__ __forceinline__ RowSplit row_split(uint32_t V, uint32_t vbase) {
+  const uint32_t to_block = (kPer - vbase % kPer) % kPer;
+  const uint32_t head = to_block < V ? to_block : V;
+  return RowSplit{head, (V - head) / kPer, (V - head) % kPer, (vbase + head) / kPer};
+}
 // ---------------------------------------------------------------------------
 // Seeds.  kW is the compile-time bound on the window width: 1 for the
 // previous-token path, kMaxWidth for wider windows (runtime width <= kW).
@@ -231,8 +266,27 @@ __device__ __forceinline__ void bias_one(T* row, uint32_t v, const RowSeed<kW>& 
   row[v] = bias_elem(row[v], delta, is_green(x, tm1));
 }
 
-// Context-seeded watermark for rows whose start is 16-byte aligned.  Grid: x = tile
-// of kThreads * kU vectors within a row, y = row (grid-stride over rows beyond
+// The columns outside whole vectors (RowSplit): the last workgroup column of a launch that
+// has any takes them, one lane a column, 16 rows a workgroup.  A path of its own, so that
+// the tiles' path keeps no registers for it (inside the tiles it cost 2-13 VGPRs a lane
+// and with them a wave per SIMD: bf16 self-salt 256 x 152064, width 4, 96 -> 106 us).
+constexpr uint32_t kEdgeRows = 16;
+static_assert(kThreads / kEdgeRows >= 14, "a row has at most 7 + 7 such columns");
+template <typename T, int kSeeding, int kW, uint32_t kPer>
+__device__ __forceinline__ void watermark_edges(T* logits, int64_t row_stride, const RowSplit& sp,
+                                                int64_t B, const int32_t* context, int width,
+                                                uint64_t key, uint32_t tm1, float delta,
+                                                uint32_t vbase, int64_t slot) {
+  const uint32_t e = threadIdx.x % (kThreads / kEdgeRows);
+  if (e >= sp.edges()) return;
+  for (int64_t row = slot * kEdgeRows + threadIdx.x / (kThreads / kEdgeRows); row < B;
+       row += static_cast<int64_t>(gridDim.y) * kEdgeRows) {
+    const RowSeed<kW> rs = row_seed<kSeeding, kW>(key, context + row * width, width);
+    bias_one<T, kSeeding>(logits + row * row_stride, sp.edge<kPer>(e), rs, tm1, delta, vbase);
+  }
+}
+
+// Context-seeded watermark.  Grid: x = tile of kThreads * kU vectors within a row, y = row (grid-stride over rows beyond
 // 65535).  Each lane issues its logits load before reading the row's window, so the
 // scalar loads of the window overlap the HBM stream.  With xcd_rows (one row per y,
 // B a multiple of 8) the workgroups are renumbered so that each of the 8 XCDs, which
@@ -243,11 +297,12 @@ __global__ void __launch_bounds__(kThreads)
 watermark_vec_kernel(T* __restrict__ logits, int64_t row_stride, uint32_t V, int64_t B,
                      const int32_t* __restrict__ context, int width, uint64_t key, uint32_t tm1,
                      float delta, uint32_t vbase, uint32_t xcd_rows) {
-  using VecT = typename std::conditional<sizeof(T) == 4, f32x4, u32x4>::type;
+  using VecT = typename VecOf<T>::Value;
+  using MemT = typename VecOf<T>::Memory;
   constexpr uint32_t kPer = 16u / sizeof(T);  // elements per 16-byte vector
-  const uint32_t full = V / kPer;             // complete vectors in a row
-  const uint32_t tail = V % kPer;
-  const uint32_t jbase = vbase / kPer;        // vector index of the first column (vbase % 8 == 0)
+  const RowSplit sp = row_split<kPer>(V, vbase);
+  const uint32_t full = sp.full;
+  const uint32_t jbase = sp.id;
   uint32_t first = blockIdx.x * (kThreads * kU);
   int64_t row0 = blockIdx.y;
   if (xcd_rows != 0u) {
@@ -256,9 +311,13 @@ watermark_vec_kernel(T* __restrict__ logits, int64_t row_stride, uint32_t V, int
     row0 = static_cast<int64_t>(q / gridDim.x) * 8 + (n & 7u);
     first = (q % gridDim.x) * (kThreads * kU);
   }
+  if (first >= full) {   // the workgroup column after the tiles
+    watermark_edges<T, kContext, kW, kPer>(logits, row_stride, sp, B, context, width, key, tm1, delta, vbase,
+                                     row0);
+    return;
+  }
   for (int64_t row = row0; row < B; row += gridDim.y) {
-    T* row_ptr = logits + row * row_stride;
-    VecT* vec = reinterpret_cast<VecT*>(row_ptr);
+    MemT* vec = reinterpret_cast<MemT*>(logits + row * row_stride + sp.head);
     const int32_t* window = context + row * width;
     VecT buf[kU];
     if (first + kThreads * kU <= full) {
@@ -283,142 +342,88 @@ watermark_vec_kernel(T* __restrict__ logits, int64_t row_stride, uint32_t V, int
         const uint32_t j = first + u * kThreads + threadIdx.x;
         if (j < full) stream_store(vec + j, bias_vec_context(buf[u], j + jbase, rs.seed, tm1, delta));
       }
-      // The partial vector at the end of the row, element by element, by lane 0 of
-      // the tile that covers vector index `full`.
-      if (tail != 0u && threadIdx.x == 0 && full >= first &&
-          full - first < static_cast<uint32_t>(kThreads * kU)) {
-        for (uint32_t e = 0; e < tail; ++e)
-          bias_one<T, kContext>(row_ptr, full * kPer + e, rs, tm1, delta, vbase);
-      }
     }
   }
 }
 
 // ---------------------------------------------------------------------------
-// Self-salt watermark over kRows rows per workgroup.  The rows of a workgroup share
-// their columns, so a candidate's J(v) and the row-independent term key*J(v)*J(v)
-// of its seed are computed once per lane and reused for every row; the window terms
-// key*J(p_i)*J(v), the minimum and the Philox draw are per row.
+// Self-salt watermark.  The rows of a workgroup share their columns, so a candidate's J(v)
+// and the row-independent term key*J(v)*J(v) of its seed are computed once per lane and
+// reused for every row; the window terms key*J(p_i)*J(v), the minimum and the Philox draw
+// are per row.
 // ---------------------------------------------------------------------------
 template <int kW>
-__device__ __forceinline__ f32x4 bias_vec_terms(f32x4 l, uint32_t j, const CandTerm (&ct)[4],
-                                                const RowSeed<kW>& rs, uint32_t tm1, float delta) {
-  const uint32_t x0 = philox_block_lane<6>(j, key_of(self_salt_seed_t(rs, ct[0]))).w0;
-  const uint32_t x1 = philox_block_lane<6>(j, key_of(self_salt_seed_t(rs, ct[1]))).w1;
-  const uint32_t x2 = philox_block_lane<6>(j, key_of(self_salt_seed_t(rs, ct[2]))).w2;
-  const uint32_t x3 = philox_block_lane<6>(j, key_of(self_salt_seed_t(rs, ct[3]))).w3;
-  f32x4 o;
-  o.x = bias_f32(l.x, delta, is_green(x0, tm1));
-  o.y = bias_f32(l.y, delta, is_green(x1, tm1));
-  o.z = bias_f32(l.z, delta, is_green(x2, tm1));
-  o.w = bias_f32(l.w, delta, is_green(x3, tm1));
-  return o;
+__device__ __forceinline__ void quad_draws(uint32_t (&x)[4], uint32_t c, const CandTerm (&ct)[4],
+                                           const RowSeed<kW>& rs) {
+  x[0] = philox_block_lane<6>(c, key_of(self_salt_seed_t(rs, ct[0]))).w0;
+  x[1] = philox_block_lane<6>(c, key_of(self_salt_seed_t(rs, ct[1]))).w1;
+  x[2] = philox_block_lane<6>(c, key_of(self_salt_seed_t(rs, ct[2]))).w2;
+  x[3] = philox_block_lane<6>(c, key_of(self_salt_seed_t(rs, ct[3]))).w3;
+}
+__device__ __forceinline__ f32x4 bias_quad(f32x4 l, const uint32_t (&x)[4], uint32_t tm1, float delta) {
+  return f32x4{bias_f32(l.x, delta, is_green(x[0], tm1)), bias_f32(l.y, delta, is_green(x[1], tm1)),
+               bias_f32(l.z, delta, is_green(x[2], tm1)), bias_f32(l.w, delta, is_green(x[3], tm1))};
+}
+__device__ __forceinline__ u32x2 bias_quad(u32x2 l, const uint32_t (&x)[4], uint32_t tm1, float delta) {
+  return u32x2{bias_bf16x2(l.x, delta, is_green(x[0], tm1), is_green(x[1], tm1)),
+               bias_bf16x2(l.y, delta, is_green(x[2], tm1), is_green(x[3], tm1))};
 }
 
-template <int kW>
-__device__ __forceinline__ u32x4 bias_vec_terms(u32x4 raw, uint32_t j, const CandTerm (&ct)[8],
-                                                const RowSeed<kW>& rs, uint32_t tm1, float delta) {
-  uint32_t x[8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e)
-    x[e] = block_word(philox_block_lane<6>(2u * j + static_cast<uint32_t>(e >> 2),
-                                           key_of(self_salt_seed_t(rs, ct[e]))),
-                      static_cast<uint32_t>(e & 3));
-  const uint32_t in[4] = {raw.x, raw.y, raw.z, raw.w};
-  uint32_t out[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q)
-    out[q] = bias_bf16x2(in[q], delta, is_green(x[2 * q], tm1), is_green(x[2 * q + 1], tm1));
-  return u32x4{out[0], out[1], out[2], out[3]};
-}
-
-// Grid: x = tile of kThreads * kU vectors of a row, y = a slot that takes groups of
-// kRows rows y, y + gridDim.y, ...  The candidate terms depend on the columns only, so
-// a workgroup computes them once, while its first group's loads are in flight, and
-// uses them for every group it takes.  With kPrefetch the next group's logits are
-// loaded while the current group is drawn.
-template <typename T, int kU, int kW, int kRows, bool kPrefetch>
+// Grid: x = tile of kThreads * kU quads of a row, y = a slot that takes the rows y,
+// y + gridDim.y, ...  The candidate terms depend on the columns only, so a workgroup
+// computes them once, while its first row's loads are in flight, and uses them for every
+// row it takes.  Bound by VALU issue: at width 4 a logit costs about 75 instructions, 51
+// of them its Philox block.  The window is a template parameter, so the minimum is a
+// straight chain that the compiler interleaves over a quad's four tokens (with a runtime
+// width the chain branched and each compare waited out its hazard: 64 x 151936 fp32, width
+// 4, 25.0 against 23.4 us).  bf16 takes 8-byte quads, not 16-byte vectors: half the terms
+// per lane, 8 waves per SIMD instead of 4 (96.8 -> 77.9 us at 256 x 152064, width 4).
+// Several rows at once per workgroup (their loads and draws side by side) measured slower
+// than one after another at every size.
+template <typename T, int kU, int kW>
 __global__ void __launch_bounds__(kThreads)
 watermark_ss_rows_kernel(T* __restrict__ logits, int64_t row_stride, uint32_t V, int64_t B,
-                         const int32_t* __restrict__ context, int width, uint64_t key, uint32_t tm1,
-                         float delta, uint32_t vbase) {
-  using VecT = typename std::conditional<sizeof(T) == 4, f32x4, u32x4>::type;
-  constexpr uint32_t kPer = 16u / sizeof(T);
-  const uint32_t full = V / kPer;
-  const uint32_t tail = V % kPer;
+                         const int32_t* __restrict__ context, uint64_t key, uint32_t tm1, float delta,
+                         uint32_t vbase) {
+  using QuadT = typename QuadOf<T>::Value;
+  using MemT = typename QuadOf<T>::Memory;
+  const RowSplit sp = row_split<4>(V, vbase);
+  const uint32_t full = sp.full;
   const uint32_t first = blockIdx.x * (kThreads * kU);
-  // the tile's first vector counted in token ids (vbase is a multiple of kPer)
-  const uint32_t id_first = first + vbase / kPer;
+  const uint32_t id_first = first + sp.id;   // the tile's first quad counted in token ids
   const bool whole = first + kThreads * kU <= full;
-  const int64_t groups = (B + kRows - 1) / kRows;
-  auto load_group = [&](VecT (&buf)[kRows][kU], int64_t g) {
-    const int64_t row0 = g * kRows;
+  if (first >= full) {   // the workgroup column after the tiles
+    watermark_edges<T, kSelfSalt, kW, 4>(logits, row_stride, sp, B, context, kW, key, tm1, delta, vbase,
+                                         blockIdx.y);
+    return;
+  }
+  CandTerm ct[kU][4];
+  bool have_terms = false;
+  for (int64_t row = blockIdx.y; row < B; row += gridDim.y) {
+    MemT* quads = reinterpret_cast<MemT*>(logits + row * row_stride + sp.head);
+    QuadT buf[kU];
 #pragma unroll
-    for (int r = 0; r < kRows; ++r) {
-      if (row0 + r < B) {
-        const VecT* vec = reinterpret_cast<const VecT*>(logits + (row0 + r) * row_stride);
+    for (int u = 0; u < kU; ++u) {
+      const uint32_t j = first + u * kThreads + threadIdx.x;
+      if (whole || j < full) buf[u] = stream_load(quads + j);
+    }
+    if (!have_terms) {
+      have_terms = true;
 #pragma unroll
-        for (int u = 0; u < kU; ++u) {
-          const uint32_t j = first + u * kThreads + threadIdx.x;
-          if (whole || j < full) buf[r][u] = stream_load(vec + j);
-        }
+      for (int u = 0; u < kU; ++u)
+#pragma unroll
+        for (uint32_t e = 0; e < 4u; ++e)
+          ct[u][e] = cand_term(key, (id_first + u * kThreads + threadIdx.x) * 4u + e);
+    }
+    const RowSeed<kW> rs = row_seed<kSelfSalt, kW>(key, context + row * kW, kW);
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      const uint32_t j = first + u * kThreads + threadIdx.x;
+      if (whole || j < full) {
+        uint32_t x[4];
+        quad_draws(x, id_first + u * kThreads + threadIdx.x, ct[u], rs);
+        stream_store(quads + j, bias_quad(buf[u], x, tm1, delta));
       }
-    }
-  };
-  CandTerm ct[kU][kPer];
-  auto draw_group = [&](const VecT (&buf)[kRows][kU], int64_t g) {
-    const int64_t row0 = g * kRows;
-#pragma unroll
-    for (int r = 0; r < kRows; ++r) {
-      if (row0 + r < B) {
-        const int64_t row = row0 + r;
-        T* row_ptr = logits + row * row_stride;
-        VecT* vec = reinterpret_cast<VecT*>(row_ptr);
-        const RowSeed<kW> rs = row_seed<kSelfSalt, kW>(key, context + row * width, width);
-#pragma unroll
-        for (int u = 0; u < kU; ++u) {
-          const uint32_t j = first + u * kThreads + threadIdx.x;
-          if (whole || j < full)
-            stream_store(vec + j, bias_vec_terms(buf[r][u], id_first + u * kThreads + threadIdx.x,
-                                                 ct[u], rs, tm1, delta));
-        }
-        // the row's partial last vector, by lane 0 of the tile that covers it
-        if (!whole && tail != 0u && threadIdx.x == 0 && full >= first &&
-            full - first < static_cast<uint32_t>(kThreads * kU)) {
-          for (uint32_t e = 0; e < tail; ++e)
-            bias_one<T, kSelfSalt>(row_ptr, full * kPer + e, rs, tm1, delta, vbase);
-        }
-      }
-    }
-  };
-  int64_t g = blockIdx.y;
-  if (g >= groups) return;
-  VecT buf0[kRows][kU];
-  load_group(buf0, g);
-#pragma unroll
-  for (int u = 0; u < kU; ++u)
-#pragma unroll
-    for (uint32_t e = 0; e < kPer; ++e)
-      ct[u][e] = cand_term(key, (id_first + u * kThreads + threadIdx.x) * kPer + e);
-  if constexpr (!kPrefetch) {
-    for (;;) {
-      draw_group(buf0, g);
-      g += gridDim.y;
-      if (g >= groups) break;
-      load_group(buf0, g);
-    }
-  } else {
-    VecT buf1[kRows][kU];
-    for (;;) {
-      const int64_t g1 = g + gridDim.y;
-      if (g1 < groups) load_group(buf1, g1);
-      draw_group(buf0, g);
-      if (g1 >= groups) break;
-      const int64_t g2 = g1 + gridDim.y;
-      if (g2 < groups) load_group(buf0, g2);
-      draw_group(buf1, g1);
-      if (g2 >= groups) break;
-      g = g2;
     }
   }
 }
@@ -600,25 +605,31 @@ __device__ __forceinline__ void slab_positions(SlabLds<kRows, kPer>& s, int rows
 
 // Grid: x = tile of kThreads vectors (4 waves of 256 vectors), y = a slot taking the
 // slabs y, y + gridDim.y, ... of kRows rows.  T: float (4 tokens a vector) or bf16
-// bits (8).  Rows 16-byte aligned; vbase a multiple of the tokens per vector.
+// bits (8).
 template <typename T, int kRows>
 __global__ void __launch_bounds__(kThreads)
 watermark_ss_slab_kernel(T* __restrict__ logits, int64_t row_stride, uint32_t V, int64_t B,
                          const int32_t* __restrict__ context, uint64_t key, uint32_t tm1,
                          float delta, uint32_t vbase) {
-  using VecT = typename std::conditional<sizeof(T) == 4, f32x4, u32x4>::type;
+  using VecT = typename VecOf<T>::Value;
+  using MemT = typename VecOf<T>::Memory;
   constexpr int kPer = 16 / sizeof(T);  // tokens a vector
   constexpr int kWords = kPer / 4;      // map words (and Philox counters) a vector
   __shared__ SlabLds<kRows, kPer> lds[kThreads / 64];
   const uint32_t lane = threadIdx.x & 63u;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   SlabLds<kRows, kPer>& s = lds[wave];
-  const uint32_t full = V / kPer;
-  const uint32_t tail = V % kPer;
+  const RowSplit sp = row_split<kPer>(V, vbase);
+  const uint32_t full = sp.full;
+  if (blockIdx.x * kThreads >= full) {   // the workgroup column after the tiles
+    watermark_edges<T, kSelfSalt, 1, kPer>(logits, row_stride, sp, B, context, 1, key, tm1, delta, vbase,
+                                     blockIdx.y);
+    return;
+  }
   const uint32_t j0 = blockIdx.x * kThreads + wave * 64u;  // the wave's first vector
   const uint32_t j = j0 + lane;
   const bool active = j < full;
-  const uint32_t jid0 = j0 + vbase / kPer;  // in token ids / kPer
+  const uint32_t jid0 = j0 + sp.id;  // in token ids / kPer
   const uint32_t jid = jid0 + lane;
   // the lane's tokens: J(v), and the self term as the queueing bound (0, which no row
   // term is below, for a lane past the row's last whole vector)
@@ -643,6 +654,7 @@ watermark_ss_slab_kernel(T* __restrict__ logits, int64_t row_stride, uint32_t V,
           static_cast<uint32_t>(is_green(word_of<3>(philox_block_lane<6>(c, key_of(self[4 * w + 3]))), tm1)) << 24;
     }
   }
+  T* first_vec = logits + sp.head;
   const int64_t slabs = (B + kRows - 1) / kRows;
   for (int64_t g = blockIdx.y; g < slabs; g += gridDim.y) {
     const int64_t row0 = g * kRows;
@@ -667,7 +679,7 @@ watermark_ss_slab_kernel(T* __restrict__ logits, int64_t row_stride, uint32_t V,
 #pragma unroll
         for (int k = 0; k < kSlabLoadRows; ++k) {
           if (r0 + k < rows) {
-            buf[k] = stream_load(reinterpret_cast<const VecT*>(logits + (row0 + r0 + k) * row_stride) + j);
+            buf[k] = stream_load(reinterpret_cast<const MemT*>(first_vec + (row0 + r0 + k) * row_stride) + j);
 #pragma unroll
             for (int w = 0; w < kWords; ++w)
               dec[k][w] = s.map[(static_cast<uint32_t>(r0 + k) * kSlabMapStride + lane) * kWords + w];
@@ -676,35 +688,12 @@ watermark_ss_slab_kernel(T* __restrict__ logits, int64_t row_stride, uint32_t V,
 #pragma unroll
         for (int k = 0; k < kSlabLoadRows; ++k) {
           if (r0 + k < rows)
-            stream_store(reinterpret_cast<VecT*>(logits + (row0 + r0 + k) * row_stride) + j,
+            stream_store(reinterpret_cast<MemT*>(first_vec + (row0 + r0 + k) * row_stride) + j,
                          slab_bias(buf[k], delta, dec[k]));
         }
       }
     }
-    // the rows' partial last vector, by lane 0 of the wave that covers it
-    if (tail != 0u && lane == 0u && full >= j0 && full - j0 < 64u) {
-      for (int r = 0; r < rows; ++r) {
-        const RowSeed<1> rs = row_seed<kSelfSalt, 1>(key, context + row0 + r, 1);
-        for (uint32_t e = 0; e < tail; ++e)
-          bias_one<T, kSelfSalt>(logits + (row0 + r) * row_stride, full * kPer + e, rs, tm1,
-                                 delta, vbase);
-      }
-    }
     __builtin_amdgcn_wave_barrier();  // the next slab rewrites the map
-  }
-}
-
-// Element-wise watermark for rows that are not 16-byte aligned.
-template <typename T, int kSeeding, int kW>
-__global__ void __launch_bounds__(kThreads)
-watermark_elem_kernel(T* __restrict__ logits, int64_t row_stride, uint32_t V, int64_t B,
-                      const int32_t* __restrict__ context, int width, uint64_t key, uint32_t tm1,
-                      float delta, uint32_t vbase) {
-  const uint32_t v = blockIdx.x * kThreads + threadIdx.x;
-  for (int64_t row = blockIdx.y; row < B; row += gridDim.y) {
-    if (v >= V) continue;
-    const RowSeed<kW> rs = row_seed<kSeeding, kW>(key, context + row * width, width);
-    bias_one<T, kSeeding>(logits + row * row_stride, v, rs, tm1, delta, vbase);
   }
 }
 
@@ -1793,125 +1782,118 @@ sbw_status_t check_width(int64_t width) {
   return SBW_OK;
 }
 
-// Vectors per lane.  Two in flight per lane measured best for the context pass (~80 %
-// of HBM peak; one per lane: ~75 %) and for fp32 self-salt (two independent sets of
-// Philox chains per lane); bf16 self-salt does best with one (8 tokens) per lane and
-// row groups that load their successor while drawing.
-template <int kSeeding, typename T>
-constexpr int unroll_for() {
-  return kSeeding == kContext
-             ? (sizeof(T) == 4 ? SBW_CONTEXT_UNROLL : SBW_CONTEXT_UNROLL_BF16)
-             : (sizeof(T) == 4 ? SBW_SELF_SALT_UNROLL : SBW_SELF_SALT_UNROLL_BF16);
+// Self-salt row kernel: one quad per lane below this many workgroups of two (B = 64 rows
+// of 19008, 640 workgroups: 5.6 us either way at width 4, 4.6 / 5.0 with one / two at width
+// 1; 16 rows of 128256, 1008: 7.5 / 6.9 us at width 4).
+constexpr int64_t kTwoQuadMinGroups = 960;
+
+// Rows that a workgroup of the self-salt row kernel takes in turn with the candidate terms
+// of its columns computed once.  A row costs 1, the terms a third of one; a CU runs its
+// share of the workgroups side by side at a fixed rate, so a launch takes as long as the
+// CU with the most: ceil(workgroups / 256) * (rows + 1/3).  The least of it over 1-8 rows
+// with at least 4 workgroups for most CUs (fewer leave latency bare).  Width 4 fp32, rows
+// 1 / 2 / 3 / 4: 64 x 151936 26.9 / 25.0 / 24.1 / 23.4 us, 128 x 50000 18.7 / 17.8 / 18.5 /
+// 19.6 us, 256 x 152064 (1 / 4 / 6 / 8) 99.0 / 85.8 / 83.9 / 87.0 us.
+int64_t rows_per_slot(int64_t tiles, int64_t B) {
+  int64_t best = 1, best_cost = INT64_MAX;
+  for (int64_t rows = 1; rows <= 8; ++rows) {
+    const int64_t groups = tiles * ((B + rows - 1) / rows);
+    if (rows > 1 && groups < kTwoQuadMinGroups) break;
+    const int64_t cost = (groups + 255) / 256 * (3 * rows + 1);
+    if (cost < best_cost) {
+      best = rows;
+      best_cost = cost;
+    }
+  }
+  return best;
 }
 
 template <typename T, int kSeeding, int kW>
 void launch_watermark(void* logits, int64_t B, uint32_t V, int64_t row_stride,
                       const int32_t* context, int width, uint64_t key, uint32_t tm1, float delta,
-                      uint32_t vbase, bool aligned, hipStream_t stream) {
+                      uint32_t vbase, hipStream_t stream) {
   T* p = static_cast<T*>(logits);
   const uint32_t rows = static_cast<uint32_t>(B < kMaxGridY ? B : kMaxGridY);
-  if (aligned) {
-    constexpr int kU = unroll_for<kSeeding, T>();
-    constexpr uint32_t kPer = 16u / sizeof(T);
-    const uint64_t vectors = (static_cast<uint64_t>(V) + kPer - 1) / kPer;
-    const uint32_t tiles = static_cast<uint32_t>((vectors + kThreads * kU - 1) / (kThreads * kU));
-    if constexpr (kSeeding == kSelfSalt) {
-      if constexpr (SBW_SELF_SALT_SLAB && kW == 1) {
-        const uint32_t tiles1 = static_cast<uint32_t>((vectors + kThreads - 1) / kThreads);
-        const int64_t slabs12 = (B + 11) / 12, slabs8 = (B + 7) / 8, slabs6 = (B + 5) / 6;
-        if (static_cast<int64_t>(tiles1) * slabs12 >= int64_t{SBW_SLAB12_MIN_GROUPS}) {
-          const dim3 grid(tiles1, static_cast<uint32_t>(slabs12 < kMaxGridY ? slabs12 : kMaxGridY));
-          hipLaunchKernelGGL((watermark_ss_slab_kernel<T, 12>), grid, dim3(kThreads), 0, stream, p,
-                             row_stride, V, B, context, key, tm1, delta, vbase);
-          return;
-        }
-        if (static_cast<int64_t>(tiles1) * slabs8 >= int64_t{SBW_SLAB_MIN_GROUPS}) {
-          const dim3 grid(tiles1, static_cast<uint32_t>(slabs8 < kMaxGridY ? slabs8 : kMaxGridY));
-          hipLaunchKernelGGL((watermark_ss_slab_kernel<T, 8>), grid, dim3(kThreads), 0, stream, p,
-                             row_stride, V, B, context, key, tm1, delta, vbase);
-          return;
-        }
-        if (static_cast<int64_t>(tiles1) * slabs6 >= int64_t{SBW_SLAB_MIN_GROUPS}) {
-          const dim3 grid(tiles1, static_cast<uint32_t>(slabs6 < kMaxGridY ? slabs6 : kMaxGridY));
-          hipLaunchKernelGGL((watermark_ss_slab_kernel<T, 6>), grid, dim3(kThreads), 0, stream, p,
-                             row_stride, V, B, context, key, tm1, delta, vbase);
-          return;
-        }
+  constexpr uint32_t kPer = 16u / sizeof(T);
+  const RowSplit sp = row_split<kPer>(V, vbase);
+  const uint64_t vectors = sp.full;
+  const uint32_t edge = sp.head + sp.tail != 0u ? 1u : 0u;   // a workgroup column for the edges
+  if constexpr (kSeeding == kSelfSalt) {
+    if constexpr (SBW_SELF_SALT_SLAB && kW == 1) {
+      const uint32_t tiles1 = static_cast<uint32_t>((vectors + kThreads - 1) / kThreads);
+      auto launch_slab = [&](auto height) -> bool {
+        constexpr int kRows = decltype(height)::value;
+        const int64_t slabs = (B + kRows - 1) / kRows;
+        const int64_t least = sizeof(T) == 2 ? SBW_SLAB_BF16_MIN_GROUPS
+                              : kRows == 12  ? SBW_SLAB12_MIN_GROUPS : SBW_SLAB_MIN_GROUPS;
+        if (static_cast<int64_t>(tiles1) * slabs < least) return false;
+        const dim3 grid(tiles1 + edge, static_cast<uint32_t>(slabs < kMaxGridY ? slabs : kMaxGridY));
+        hipLaunchKernelGGL((watermark_ss_slab_kernel<T, kRows>), grid, dim3(kThreads), 0, stream, p,
+                           row_stride, V, B, context, key, tm1, delta, vbase);
+        return true;
+      };
+      if (launch_slab(std::integral_constant<int, 12>{})) return;
+      if constexpr (sizeof(T) == 4) {
+        if (launch_slab(std::integral_constant<int, 8>{})) return;
+        if (launch_slab(std::integral_constant<int, 6>{})) return;
       }
-      constexpr int kMaxRows = kW > 1 ? 1 : (sizeof(T) == 4 ? 4 : 2);
-      const int64_t work = static_cast<int64_t>(tiles) * B;
-      if constexpr (kMaxRows == 4) {
-        // fp32, width 1: 4-row groups take one vector per lane, whenever that makes
-        // SBW_SELF_SALT_MIN_GROUPS workgroups (the narrower tiles keep more of them
-        // resident at once than two vectors per lane do)
-        const uint32_t tiles1 = static_cast<uint32_t>((vectors + kThreads - 1) / kThreads);
-        if (static_cast<int64_t>(tiles1) * B >= 4 * int64_t{SBW_SELF_SALT_MIN_GROUPS}) {
-          const int64_t groups = (B + 3) / 4;
-          const dim3 grid(tiles1, static_cast<uint32_t>(groups < kMaxGridY ? groups : kMaxGridY));
-          hipLaunchKernelGGL((watermark_ss_rows_kernel<T, 1, kW, 4, false>), grid, dim3(kThreads),
-                             0, stream, p, row_stride, V, B, context, width, key, tm1, delta,
-                             vbase);
-          return;
-        }
-      }
-      const int rows_per_group =
-          (kMaxRows >= 2 && work >= 2 * int64_t{SBW_SELF_SALT_MIN_GROUPS}) ? 2 : 1;
-      const int64_t groups = (B + rows_per_group - 1) / rows_per_group;
-      // Each workgroup takes up to kIters groups while that still leaves
-      // SBW_SELF_SALT_MIN_GROUPS workgroups.
-      int64_t slots = groups;
-      constexpr int kIters = sizeof(T) == 4 ? SBW_SELF_SALT_GROUP_ITERS : SBW_SELF_SALT_GROUP_ITERS_BF16;
-      for (int it = kIters; it > 1; --it) {
-        const int64_t s2 = (groups + it - 1) / it;
-        if (s2 * tiles >= int64_t{SBW_SELF_SALT_MIN_GROUPS}) { slots = s2; break; }
-      }
-      const dim3 grid(tiles, static_cast<uint32_t>(slots < kMaxGridY ? slots : kMaxGridY));
-      constexpr bool kPf = (sizeof(T) == 4 ? SBW_SELF_SALT_PREFETCH : SBW_SELF_SALT_PREFETCH_BF16) != 0;
-      if (kMaxRows >= 2 && rows_per_group == 2)
-        hipLaunchKernelGGL((watermark_ss_rows_kernel<T, kU, kW, (kMaxRows >= 2 ? 2 : 1), kPf>), grid,
-                           dim3(kThreads), 0, stream, p, row_stride, V, B, context, width, key, tm1,
-                           delta, vbase);
-      else
-        hipLaunchKernelGGL((watermark_ss_rows_kernel<T, kU, kW, 1, kPf>), grid, dim3(kThreads), 0,
-                           stream, p, row_stride, V, B, context, width, key, tm1, delta, vbase);
-    } else {
-      // whole rows per XCD for large launches (one launch row per grid row, workgroup
-      // numbers below 2^32)
-      const uint32_t xcd_rows =
-          B >= SBW_XCD_ROWS_MIN && B % 8 == 0 && B <= kMaxGridY &&
-                  B * static_cast<int64_t>(V) * static_cast<int64_t>(sizeof(T)) >= SBW_XCD_ROWS_MIN_BYTES &&
-                  static_cast<uint64_t>(tiles) * static_cast<uint64_t>(B) < (uint64_t{1} << 32)
-              ? 1u
-              : 0u;
-      hipLaunchKernelGGL((watermark_vec_kernel<T, kU, kW>), dim3(tiles, rows),
-                         dim3(kThreads), 0, stream, p, row_stride, V, B, context, width, key, tm1,
-                         delta, vbase, xcd_rows);
     }
+    const RowSplit quads = row_split<4>(V, vbase);
+    const uint32_t quad_edge = quads.head + quads.tail != 0u ? 1u : 0u;
+    const uint32_t tiles2 = (quads.full + 2 * kThreads - 1) / (2 * kThreads);
+    if (tiles2 * B < kTwoQuadMinGroups) {
+      const dim3 grid((quads.full + kThreads - 1) / kThreads + quad_edge, rows);
+      hipLaunchKernelGGL((watermark_ss_rows_kernel<T, 1, kW>), grid, dim3(kThreads), 0, stream, p,
+                         row_stride, V, B, context, key, tm1, delta, vbase);
+      return;
+    }
+    const int64_t slots = (B + rows_per_slot(tiles2, B) - 1) / rows_per_slot(tiles2, B);
+    const dim3 grid(tiles2 + quad_edge, static_cast<uint32_t>(slots < kMaxGridY ? slots : kMaxGridY));
+    hipLaunchKernelGGL((watermark_ss_rows_kernel<T, 2, kW>), grid, dim3(kThreads), 0, stream, p,
+                       row_stride, V, B, context, key, tm1, delta, vbase);
   } else {
-    const uint32_t tiles = static_cast<uint32_t>((static_cast<uint64_t>(V) + kThreads - 1) / kThreads);
-    hipLaunchKernelGGL((watermark_elem_kernel<T, kSeeding, kW>), dim3(tiles, rows), dim3(kThreads),
-                       0, stream, p, row_stride, V, B, context, width, key, tm1, delta, vbase);
+    // Two vectors in flight per lane measured best (~80 % of HBM peak; one: ~75 %).
+    constexpr int kU = sizeof(T) == 4 ? SBW_CONTEXT_UNROLL : SBW_CONTEXT_UNROLL_BF16;
+    const uint32_t tiles = static_cast<uint32_t>((vectors + kThreads * kU - 1) / (kThreads * kU));
+    // whole rows per XCD for large launches (one launch row per grid row, workgroup
+    // numbers below 2^32)
+    const uint32_t xcd_rows =
+        B >= SBW_XCD_ROWS_MIN && B % 8 == 0 && B <= kMaxGridY &&
+                B * static_cast<int64_t>(V) * static_cast<int64_t>(sizeof(T)) >= SBW_XCD_ROWS_MIN_BYTES &&
+                (uint64_t{tiles} + edge) * static_cast<uint64_t>(B) < (uint64_t{1} << 32)
+            ? 1u
+            : 0u;
+    hipLaunchKernelGGL((watermark_vec_kernel<T, kU, kW>), dim3(tiles + edge, rows),
+                       dim3(kThreads), 0, stream, p, row_stride, V, B, context, width, key, tm1,
+                       delta, vbase, xcd_rows);
   }
 }
 
 template <typename T>
 void dispatch_watermark(void* logits, int64_t B, uint32_t V, int64_t row_stride,
                         const int32_t* context, int width, uint64_t key, uint32_t tm1, float delta,
-                        sbw_seeding_t seeding, uint32_t vbase, bool aligned, hipStream_t st) {
+                        sbw_seeding_t seeding, uint32_t vbase, hipStream_t st) {
   // Context seeding folds any window into one row seed; self-salt needs the window
   // per candidate, so wider windows take the kMaxWidth instantiation.
   if (seeding == SBW_SEED_CONTEXT)
     launch_watermark<T, kContext, kMaxWidth>(logits, B, V, row_stride, context, width, key, tm1,
-                                             delta, vbase, aligned, st);
-  else if (width == 1)
-    launch_watermark<T, kSelfSalt, 1>(logits, B, V, row_stride, context, width, key, tm1, delta,
-                                      vbase, aligned, st);
-  else if (width <= kMidWidth)
-    launch_watermark<T, kSelfSalt, kMidWidth>(logits, B, V, row_stride, context, width, key, tm1,
-                                              delta, vbase, aligned, st);
-  else
-    launch_watermark<T, kSelfSalt, kMaxWidth>(logits, B, V, row_stride, context, width, key, tm1,
-                                              delta, vbase, aligned, st);
+                                             delta, vbase, st);
+  else {
+    auto launch = [&](auto w) {
+      launch_watermark<T, kSelfSalt, decltype(w)::value>(logits, B, V, row_stride, context, width, key,
+                                                         tm1, delta, vbase, st);
+    };
+    switch (width) {
+      case 1: launch(std::integral_constant<int, 1>{}); break;
+      case 2: launch(std::integral_constant<int, 2>{}); break;
+      case 3: launch(std::integral_constant<int, 3>{}); break;
+      case 4: launch(std::integral_constant<int, 4>{}); break;
+      case 5: launch(std::integral_constant<int, 5>{}); break;
+      case 6: launch(std::integral_constant<int, 6>{}); break;
+      case 7: launch(std::integral_constant<int, 7>{}); break;
+      default: launch(std::integral_constant<int, 8>{}); break;
+    }
+  }
 }
 
 template <typename T>
@@ -2312,17 +2294,16 @@ sbw_status_t sbw_watermark_shard(void* logits, sbw_dtype_t dtype, int64_t B, int
   if (s != SBW_OK) return s;
 
   const uint32_t vbase = static_cast<uint32_t>(v_offset);
-  const bool aligned = vector_path_ok(logits, row_stride, dtype, vbase);
   const uint32_t tm1 = static_cast<uint32_t>(T - 1);
   const uint32_t v32 = static_cast<uint32_t>(V);
   const int w = static_cast<int>(width);
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (dtype == SBW_F32)
     dispatch_watermark<float>(logits, B, v32, row_stride, context, w, key, tm1, delta, seeding,
-                              vbase, aligned, st);
+                              vbase, st);
   else
     dispatch_watermark<uint16_t>(logits, B, v32, row_stride, context, w, key, tm1, delta, seeding,
-                                 vbase, aligned, st);
+                                 vbase, st);
   return after_launch();
 }
 
@@ -2434,7 +2415,6 @@ sbw_status_t sbw_watermark_argmax_noalloc(const void* logits, sbw_dtype_t dtype,
 
 int64_t sbw_watermark_argmax_workspace(int64_t B, int64_t V) {
   if (B <= 0 || V <= 0) return 0;
-  // the element path has the most segments per row (the vector paths fewer)
   return B * ((V + kArgmaxSegElems - 1) / kArgmaxSegElems);
 }
 

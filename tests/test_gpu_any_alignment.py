@@ -1,0 +1,83 @@
+"""GPU parity of the watermark on rows and shards that start anywhere.
+
+Logits move in 16-byte vectors (self-salt: 4-token quads) from any element address, with
+the columns before the first whole Philox block and after the last one taken one by one.
+The cases cover every start modulo 8 of a shard, rows shorter than a vector, rows one
+column either side of whole vectors and tiles, odd row strides and base offsets, windows of
+1-8 tokens (each its own self-salt kernel), one and two quads per lane, and workgroups that
+take several rows.  Logits bit for bit against the oracle, and nothing outside the shard's
+columns may change.
+"""
+import numpy as np
+import pytest
+
+import oracle
+import workloads
+from test_gpu_parity import WIDE, assert_logits_equal, env, say, special_logits, _from_device, _to_device  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+def check(env, dtype, seeding, width, B, start, n, offset=0, pad=0, gamma=0.25, delta=2.0):
+    """A shard of columns start .. start + n - 1, in rows of n + pad elements that begin
+    `offset` elements into a buffer."""
+    torch, sbw, dev = env
+    rng = np.random.default_rng(B * 31 + start * 7 + n + width + offset)
+    full = special_logits(rng, B, start + n, "f32")
+    if dtype == "bf16":
+        full = workloads.f32_to_bf16_bits(full)
+    ctx = workloads.context_tokens(B, width, start + n, rng)
+    stride = n + pad
+    base = np.zeros(offset + B * stride + 16, dtype=full.dtype)
+    base[:] = 3
+    rows = np.lib.stride_tricks.as_strided(base[offset:], shape=(B, n),
+                                           strides=(stride * base.itemsize, base.itemsize))
+    rows[...] = full[:, start:]
+    expect = base.copy()
+    np.lib.stride_tricks.as_strided(expect[offset:], shape=(B, n),
+                                    strides=(stride * base.itemsize, base.itemsize))[...] = \
+        oracle.watermark_w(full, ctx, WIDE, gamma, delta, seeding)[:, start:]
+    t = _to_device(torch, dev, base)
+    c = torch.from_numpy(np.ascontiguousarray(ctx, dtype=np.int32)).to(dev)
+    what = f"{dtype} {seeding} h={width} B={B} start={start} n={n} offset={offset} pad={pad}"
+    say("any alignment " + what)
+    sbw.watermark_shard(t[offset:offset + B * stride].view(B, stride)[:, :n], c, start, WIDE, gamma, delta,
+                        seeding)
+    torch.cuda.synchronize()
+    assert_logits_equal(_from_device(torch, t)[None], expect[None], what)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("seeding", ["context", "self_salt"])
+@pytest.mark.parametrize("width", [1, 3, 8])
+def test_every_start_and_short_rows(env, dtype, seeding, width):
+    for start in range(9):
+        for n in (1, 2, 5, 8, 9, 15, 23, 1027, 4101):
+            check(env, dtype, seeding, width, 5, start, n, offset=start % 3, pad=n % 4)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("seeding", ["context", "self_salt"])
+@pytest.mark.parametrize("n", [4095, 4096, 4097, 8191, 8193])
+def test_tile_edges(env, dtype, seeding, n):
+    for start, offset, pad in [(0, 0, 0), (0, 1, 1), (1003, 0, 3), (1004, 5, 0)]:
+        check(env, dtype, seeding, 2, 37, start, n, offset, pad)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("width", [1, 2, 3, 4, 5, 6, 7, 8])
+def test_self_salt_rows_in_turn(env, dtype, width):
+    """Enough workgroups for two quads per lane and several rows each (B not a multiple)."""
+    check(env, dtype, "self_salt", width, 67, 0, 30003)
+    check(env, dtype, "self_salt", width, 143, 1025, 10241, offset=1, pad=2, delta=-1.5)
+
+
+def test_bf16_slab_from_its_line(env):
+    """bf16, window of one token: 12-row slabs from 4800 of them (here 10 tiles x 501)."""
+    check(env, "bf16", "self_salt", 1, 6005, 0, 20477, pad=2)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_context_whole_rows_per_xcd_with_edges(env, dtype):
+    """Launches large enough for whole rows per XCD, whose rows have single columns."""
+    check(env, dtype, "context", 4, 512 if dtype == "f32" else 1024, 3, 131079)
