@@ -159,20 +159,20 @@ __device__ __forceinline__ Key opaque_key(Key k) {
   return k;
 }
 
-// The ten round keys of a Philox key, for a stream drawn many times with one key.
-// Held in vector registers (opaque to the optimiser), the rounds then take them as
+// The ten round keys of a wave-uniform Philox key, for a stream drawn many times with one
+// key.  Held in scalar registers (opaque to the optimiser), the rounds then take them as
 // operands instead of deriving them again with scalar adds for every block.
 struct RoundKeys {
   uint32_t k0[10], k1[10];
 };
 
-__device__ __forceinline__ RoundKeys vector_round_keys(Key k) {
+__device__ __forceinline__ RoundKeys scalar_round_keys(Key k) {
   RoundKeys rk;
 #pragma unroll
   for (int r = 0; r < 10; ++r) {
     rk.k0[r] = k.lo + static_cast<uint32_t>(r) * kPhiloxWeyl0;
     rk.k1[r] = k.hi + static_cast<uint32_t>(r) * kPhiloxWeyl1;
-    asm volatile("" : "+v"(rk.k0[r]), "+v"(rk.k1[r]));
+    asm volatile("" : "+s"(rk.k0[r]), "+s"(rk.k1[r]));
   }
   return rk;
 }
@@ -358,20 +358,30 @@ constexpr float kGumbelHi = 17.0f;
 //  * Above: t = -log(1 - q) > q, so G = -log t < -log q <= (c + 1) ln 2.
 //  * Below, for c >= 2: G increases with u, so it exceeds its value at
 //    u = 1 - 2^-c, -log(-log(1 - 2^-c)) = c ln 2 - e(c) with e(2) = 0.1404 and e
-//    falling toward 0 as c grows; so G > gumbel_upper(c) - (ln 2 + margin + 0.1404).
-// The upper bound takes one fma; both hold, with room for the rounding of the fp32
-// logarithm, for every one of the 2^23 values of u.
+//    falling toward 0 as c grows; so G > (c + 1) ln 2 - (ln 2 + 0.1404).
+// Both hold, with room for the rounding of the fp32 logarithm, for every one of the 2^23
+// values of u.
 constexpr float kLn2f = 0.693147182f;                    // ln 2 rounded up
 constexpr float kGumbelMargin = 0.0009765625f;           // 2^-10
-constexpr float kGumbelUpperOffset = kLn2f + kGumbelMargin;
-constexpr float kGumbelGap = 0.8442f;                    // gumbel_upper(c) - G for c >= 2
+constexpr float kGumbelGap = 0.8442f;                    // (c + 1) ln 2 + margin - G for c >= 2
 
-// c as a float.  ~x | 2^8 has at most 23 leading zeros, so no cap is needed.
-__device__ __forceinline__ float noise_ones(uint32_t x) {
-  return static_cast<float>(__builtin_clz(~x | 0x100u));
-}
-__device__ __forceinline__ float gumbel_upper(float c) {
-  return __builtin_fmaf(c, kLn2f, kGumbelUpperOffset);
+// The passes take a finer form of the same bounds.  y = 2^32 q = (~x & ~511) | 256 is exact
+// in fp32, and the bits of a float read as an integer are 2^23 (127 + e + f) for the value
+// 2^e (1 + f), with log2(1 + f) in [f, f + 0.0861).  So with b those bits of y (rounded to
+// 24 significant bits when converted), -log q lies in (159 - b / 2^23) ln 2 - [0, 0.0597),
+// where 159 = 127 + 32, and
+//  * G < kNoiseBitsOffset - kNoiseBitsScale * b, the offset with the margin in it;
+//  * for q < 1/4 (so for every draw whose bound exceeds kNoiseUpperRange), G is above that
+//    bound less kNoiseGap (e(2) + 0.0597 + the margin would do; the largest gap is 0.1647).
+// Checked for every one of the 2^23 values of u, like the coarse form.
+constexpr float kNoiseBitsScale = 8.26295832e-08f;       // ln 2 / 2^23
+constexpr float kNoiseBitsOffset = 110.211402f;          // 159 ln 2 + 2^-10
+constexpr float kNoiseGap = 0.17f;
+constexpr float kNoiseUpperRange = 1.389f;               // 2 ln 2 + the margin, rounded up
+
+// b as a float.
+__device__ __forceinline__ float noise_bits(uint32_t x) {
+  return static_cast<float>(__float_as_uint(static_cast<float>((~x & 0xFFFFFE00u) | 0x100u)));
 }
 
 }  // namespace sbw

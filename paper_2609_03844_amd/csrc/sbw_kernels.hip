@@ -252,7 +252,7 @@ __device__ __forceinline__ u32x4 bias_vec_context(u32x4 raw, uint32_t j, uint64_
   return u32x4{out[0], out[1], out[2], out[3]};
 }
 
-// One element of either dtype (row tails and unaligned rows).
+// One element of either dtype (columns outside whole vectors).
 __device__ __forceinline__ float bias_elem(float l, float d, bool g) { return bias_f32(l, d, g); }
 __device__ __forceinline__ uint16_t bias_elem(uint16_t l, float d, bool g) {
   return bias_bf16(l, d, g);
@@ -706,27 +706,34 @@ watermark_ss_slab_kernel(T* __restrict__ logits, int64_t row_stride, uint32_t V,
 // orders the values (every NaN above +inf, -0 equal to +0), the low word is
 // ~index, so the maximum key is the largest value at its smallest index.
 // ---------------------------------------------------------------------------
-// 16-byte vectors per lane in a sub-batch of the fused decoding pass (greedy and
-// sampling), and sub-batches per workgroup segment.  A longer segment gives each wave
-// a larger sample for its bounds; every lane holds a sub-batch in registers, and bf16
-// takes fewer vectors to hold its 8-token bounds.
+// 16-byte vectors per lane in a sub-batch of the fused decoding pass, and sub-batches per
+// workgroup segment.  A longer segment gives each wave a larger sample for its bounds, but
+// every lane holds a sub-batch in registers.  Sampling fp32, 256 x 152064: 4 / 6 / 8 / 12
+// vectors 38.0 (two sub-batches) / 37.7 / 38.2 / 40.7 us; sampling bf16, 160 x 152064: 4 /
+// 5 / 6 / 8 vectors 26.0 / 25.4 / 25.5 / 27.9 us; greedy fp32, 256 x 152064: 28.0 us from 4
+// to 8.  Greedy bf16 takes two sub-batches, the second's loads in flight while the first
+// is scored: 900 x 152064, 4 x 1 / 2 x 2 / 3 x 2 / 3 x 4: 52.5 / 50.2 / 47.2 / 48.1 us.
 #ifndef SBW_DECODE_VECS_F32_GREEDY
-#define SBW_DECODE_VECS_F32_GREEDY 6   // greedy decoding, fp32 (sampling keeps 8)
+#define SBW_DECODE_VECS_F32_GREEDY 6
 #endif
 #ifndef SBW_DECODE_VECS_F32
-#define SBW_DECODE_VECS_F32 8
+#define SBW_DECODE_VECS_F32 6          // sampling
 #endif
 #ifndef SBW_DECODE_VECS_BF16
-#define SBW_DECODE_VECS_BF16 4
+#define SBW_DECODE_VECS_BF16 3         // greedy
 #endif
 #ifndef SBW_DECODE_VECS_BF16_SAMPLE
-#define SBW_DECODE_VECS_BF16_SAMPLE 5   // sampling, bf16 (greedy keeps 4)
+#define SBW_DECODE_VECS_BF16_SAMPLE 5
 #endif
-#ifndef SBW_DECODE_SUBS
-#define SBW_DECODE_SUBS 1
+#ifndef SBW_DECODE_SUBS_BF16
+#define SBW_DECODE_SUBS_BF16 2         // greedy; the others take one
 #endif
-constexpr int kElemSegSteps = 8;                                // element kernel
-constexpr int64_t kArgmaxSegElems = kThreads * kElemSegSteps;   // element-kernel segment
+// Greedy fp32 decoding of more than the Infinity Cache holds: unused LDS that leaves a CU 6
+// workgroups instead of 8.  With all 8 streaming, the reads crowd each other out (900 x
+// 152064: 8 / 7 / 6 / 5 of them 84.6 / 83.7 / 82.0 / 84.8 us; 256 x 152064, 27.6 / 27.4 /
+// 27.9 / 29.3; bf16 is fastest with all).
+constexpr uint32_t kCrowdedLds = 16000;
+constexpr int64_t kArgmaxSegElems = kThreads * 8;   // the shortest segment the workspace holds
 
 __device__ __forceinline__ uint32_t order_bits(float f) {
   uint32_t b = __float_as_uint(f);
@@ -739,10 +746,7 @@ __device__ __forceinline__ uint64_t arg_key(float f, uint32_t v) {
   return (static_cast<uint64_t>(order_bits(f)) << 32) | static_cast<uint32_t>(~v);
 }
 
-// Running argmax of one lane, which visits its indices in increasing order: a strict
-// greater-than keeps the first of equal values (and -0 == +0); the first NaN wins and
-// then stays.  `any` is false until the lane has seen an element.  (Measured faster
-// than a NaN-seeded form with fewer operations, and than a form without NaN handling.)
+// Running argmax of one lane.  `any` is false until the lane has seen an element.
 struct LaneBest {
   float v;
   uint32_t i;
@@ -751,17 +755,8 @@ struct LaneBest {
 
 __device__ __forceinline__ LaneBest lane_best_init() { return LaneBest{0.0f, 0u, false}; }
 
-__device__ __forceinline__ void consider(LaneBest& b, float x, uint32_t i) {
-  // Bitwise, not short-circuit, operators keep the update branch-free.
-  const bool take = static_cast<bool>(static_cast<int>(!b.any) | static_cast<int>(x > b.v) |
-                                      (static_cast<int>(x != x) & static_cast<int>(b.v == b.v)));
-  b.v = take ? x : b.v;
-  b.i = take ? i : b.i;
-  b.any = true;
-}
-
-// The same argmax for a lane that sees its indices in any order: equal values and
-// NaNs go to the smaller index.
+// The lane sees its indices in any order: a larger value wins, any NaN wins over numbers,
+// equal values (-0 == +0) and NaNs go to the smaller index.
 __device__ __forceinline__ void consider_any_order(LaneBest& b, float x, uint32_t i) {
   const int xn = static_cast<int>(x != x), bn = static_cast<int>(b.v != b.v);
   const int first = static_cast<int>(i < b.i);
@@ -824,9 +819,12 @@ __device__ __forceinline__ void wave_argmax(uint64_t& k, uint64_t& p) {
 // Block-wide argmax of the lanes' running bests; thread 0 stores the partial.
 __device__ __forceinline__ void block_argmax_store(const LaneBest& lb, uint64_t* out,
                                                    uint64_t* lds_key, uint64_t* lds_part) {
-  uint64_t k = lb.any ? arg_key(lb.v, lb.i) : 0u;
-  uint64_t p = pack_partial(lb.v, lb.i);
-  wave_argmax(k, p);
+  uint64_t k = 0u, p = 0u;
+  if (__any(lb.any)) {   // most often the queue's tokens all went to the first wave
+    k = lb.any ? arg_key(lb.v, lb.i) : 0u;
+    p = pack_partial(lb.v, lb.i);
+    wave_argmax(k, p);
+  }
   if (threadIdx.x % 64 == 0) {
     lds_key[threadIdx.x / 64] = k;
     lds_part[threadIdx.x / 64] = p;
@@ -859,18 +857,15 @@ __device__ __forceinline__ float reach_bound(float m, float delta, uint16_t) {
   return fminf(m, widen(bias_bf16(static_cast<uint16_t>(b), delta, true)));
 }
 
-// The 8 bf16 elements of a vector as (x, bias(x)) pairs: each token's two candidate
-// values, widened.
-__device__ __forceinline__ void green_values(u32x4 o, float delta, float (&x)[8], float (&gv)[8]) {
-  const uint32_t w[4] = {o.x, o.y, o.z, o.w};
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const uint32_t g = bias_bf16x2(w[q], delta, true, true);
-    x[2 * q] = __uint_as_float(w[q] << 16);
-    x[2 * q + 1] = __uint_as_float(w[q] & 0xFFFF0000u);
-    gv[2 * q] = __uint_as_float(g << 16);
-    gv[2 * q + 1] = __uint_as_float(g & 0xFFFF0000u);
-  }
+// A logit below which neither candidate value reaches lb: x + dplus, rounded (to 24 or 8
+// significant bits), is at most x + dplus + rel * (|lb| + dplus) where it reaches lb.
+// Bounds too large for the sums here keep every token.
+__device__ __forceinline__ float reach_threshold(float lb, float dplus, float) {
+  return fabsf(lb) < 1e37f && dplus < 1e37f ? (lb - dplus) - 0x1p-21f * (fabsf(lb) + dplus) : -INFINITY;
+}
+__device__ __forceinline__ float reach_threshold(float lb, float dplus, uint16_t) {
+  return fabsf(lb) < 1e37f && dplus < 1e37f ? (lb - dplus) - 0x1p-7f * (fabsf(lb) + dplus) - 0x1p-130f
+                                            : -INFINITY;
 }
 
 // What a pass maximises: the watermarked logit (greedy decoding), or, for sampling,
@@ -879,58 +874,64 @@ template <bool kSample>
 struct Score {
   uint64_t seed;    // sampling: the row's noise seed
   float inv_t;      // sampling: 1 / temperature
-  __device__ __forceinline__ float of(float l, uint32_t v) const {
-    if constexpr (kSample) return l * inv_t + gumbel_of(cbrng(v, seed));
-    return l;
-  }
 };
 
-// Each token's larger candidate logit, max(x, bias(x)), times 1/T.  fp32: bias(x)
-// is x + delta rounded, so the larger one is x + max(delta, 0) (x + 0 only turns -0
-// into +0).  bf16: bias rounds to bf16, so both candidates are formed.
-__device__ __forceinline__ void upper_logits(f32x4 o, float, float dplus, float inv_t, float (&phi)[4]) {
-  phi[0] = (o.x + dplus) * inv_t;
-  phi[1] = (o.y + dplus) * inv_t;
-  phi[2] = (o.z + dplus) * inv_t;
-  phi[3] = (o.w + dplus) * inv_t;
+// A token's larger candidate logit, max(x, bias(x)): bias(x) for a positive delta, else x;
+// either way x + dplus rounded to the logits' type, dplus = max(delta, 0) (x + 0 only turns
+// -0 into +0).  Non-decreasing in x.
+__device__ __forceinline__ float upper_logit(float x, float dplus, float) { return x + dplus; }
+__device__ __forceinline__ float upper_logit(float x, float dplus, uint16_t) {   // x: a widened bf16
+  return __uint_as_float(to_bf16x2(x + dplus, 0.0f) << 16);
 }
-__device__ __forceinline__ void upper_logits(u32x4 o, float delta, float, float inv_t, float (&phi)[8]) {
-  float x[8], gv[8];
-  green_values(o, delta, x, gv);
-#pragma unroll
-  for (int e = 0; e < 8; ++e) phi[e] = (delta >= 0.0f ? gv[e] : x[e]) * inv_t;
-}
-
-// The same without the temperature (greedy decoding).
-__device__ __forceinline__ void upper_logits(f32x4 o, float, float dplus, float (&phi)[4]) {
+__device__ __forceinline__ void upper_logits(f32x4 o, float dplus, float (&phi)[4]) {
   phi[0] = o.x + dplus;
   phi[1] = o.y + dplus;
   phi[2] = o.z + dplus;
   phi[3] = o.w + dplus;
 }
-__device__ __forceinline__ void upper_logits(u32x4 o, float delta, float, float (&phi)[8]) {
-  float x[8], gv[8];
-  green_values(o, delta, x, gv);
-#pragma unroll
-  for (int e = 0; e < 8; ++e) phi[e] = delta >= 0.0f ? gv[e] : x[e];
-}
-
-// Largest raw logit of a vector folded into m.  v_max3_f32 on the raw values: the
-// compiler's fmaxf would first canonicalise every loaded value.  A signalling NaN
-// may make m NaN, which only turns the skip test built on m off.
-__device__ __forceinline__ float max3_raw(float a, float b, float c) {
-  float r;
-  asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-  return r;
-}
-__device__ __forceinline__ float fold_max(f32x4 o, float m) {
-  return max3_raw(max3_raw(m, o.x, o.y), o.z, o.w);
-}
-__device__ __forceinline__ float fold_max(u32x4 o, float m) {
+__device__ __forceinline__ void upper_logits(u32x4 o, float dplus, float (&phi)[8]) {
   const uint32_t w[4] = {o.x, o.y, o.z, o.w};
 #pragma unroll
-  for (int q = 0; q < 4; ++q) m = max3_raw(m, __uint_as_float(w[q] << 16), __uint_as_float(w[q] & 0xFFFF0000u));
-  return m;
+  for (int q = 0; q < 4; ++q) {
+    const uint32_t g = to_bf16x2(__uint_as_float(w[q] << 16) + dplus,
+                                 __uint_as_float(w[q] & 0xFFFF0000u) + dplus);
+    phi[2 * q] = __uint_as_float(g << 16);
+    phi[2 * q + 1] = __uint_as_float(g & 0xFFFF0000u);
+  }
+}
+
+// Largest of a vector's values, NaN when one of them is.
+__device__ __forceinline__ float max3_nan(float a, float b, float c) {
+  return __builtin_elementwise_maximum(__builtin_elementwise_maximum(a, b), c);
+}
+__device__ __forceinline__ float vec_max(const float (&x)[4]) {
+  return __builtin_elementwise_maximum(max3_nan(x[0], x[1], x[2]), x[3]);
+}
+__device__ __forceinline__ float vec_max(const float (&x)[8]) {
+  return __builtin_elementwise_maximum(max3_nan(max3_nan(max3_nan(x[0], x[1], x[2]), x[3], x[4]), x[5], x[6]), x[7]);
+}
+__device__ __forceinline__ float vec_max(f32x4 o) {
+  const float x[4] = {o.x, o.y, o.z, o.w};
+  return vec_max(x);
+}
+__device__ __forceinline__ float vec_max(u32x4 o) {
+  const uint32_t w[4] = {o.x, o.y, o.z, o.w};
+  float x[8];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    x[2 * q] = __uint_as_float(w[q] << 16);
+    x[2 * q + 1] = __uint_as_float(w[q] & 0xFFFF0000u);
+  }
+  return vec_max(x);
+}
+
+// The larger of a and b; a NaN loses.  v_max_f32 on the raw values: the compiler's fmaxf
+// would first canonicalise every loaded value.  A signalling NaN may make the result NaN,
+// which only turns the skip tests built on it off.
+__device__ __forceinline__ float max_raw(float a, float b) {
+  float r;
+  asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
 }
 
 // Largest value over the wave, by DPP moves on order-preserving integer keys (no
@@ -952,6 +953,23 @@ __device__ __forceinline__ float wave_max(float v) {
   k = dpp_max_step<0x143, 0xC>(k);   // row_bcast:31 into rows 2 and 3
   k = __builtin_amdgcn_readlane(k, 63);
   return __int_as_float(k ^ ((k >> 31) & 0x7FFFFFFF));
+}
+
+__device__ __forceinline__ uint32_t raw_bits(float x) { return __float_as_uint(x); }
+__device__ __forceinline__ uint32_t raw_bits(uint16_t x) { return x; }
+
+// A vector of -inf, for the lanes past a row's last vector.
+__device__ __forceinline__ f32x4 lowest_vec(f32x4) { return f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY}; }
+__device__ __forceinline__ u32x4 lowest_vec(u32x4) { return u32x4{0xFF80FF80u, 0xFF80FF80u, 0xFF80FF80u, 0xFF80FF80u}; }
+
+// Element e of a vector, widened.
+__device__ __forceinline__ float elem(f32x4 o, int e) {
+  const float w[4] = {o.x, o.y, o.z, o.w};
+  return w[e];
+}
+__device__ __forceinline__ float elem(u32x4 o, int e) {
+  const uint32_t w[4] = {o.x, o.y, o.z, o.w};
+  return __uint_as_float((e & 1) ? (w[e >> 1] & 0xFFFF0000u) : (w[e >> 1] << 16));
 }
 
 // The raw bits of element e of a vector (fp32 bits, or bf16 bits in the low half).
@@ -1024,35 +1042,47 @@ __device__ __forceinline__ void score_queue(LaneBest& b, const uint32_t* q_v, co
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Fused decoding, vector path: greedy (kSample false) or Gumbel-max sampling.  A
-// segment is kSub sub-batches of kThreads * kN vectors, vector n of lane t at
-// offset n * kThreads + t; every lane loads a sub-batch at once.  The colour draw
-// (and, sampling, the exact noise with its two logarithms) matters only for the few
-// tokens that may still reach the wave's best score.  Per sub-batch:
+// Fused decoding: greedy (kSample false) or Gumbel-max sampling.  A segment is kSub
+// sub-batches of kThreads * kN vectors, vector n of lane t at offset n * kThreads + t; a
+// sub-batch is loaded while the one before it is scored.  The colour draw (and, sampling,
+// the exact noise with its two logarithms) matters only for the few tokens that may still
+// reach the wave's best score.  Per sub-batch:
 //  1. greedy: with m the wave's largest logit, some token ends at least at
-//     lb = min(m, bias(m)), and a token's value is at most max(x, bias(x));
-//     sampling: lb from m with the noise's overall minimum, and a vector none of
-//     whose tokens reaches lb even with the noise's overall maximum draws no noise;
-//     the other vectors draw their noise, each token's score is bounded from above
-//     and below by the bounds of its noise (gumbel_upper, kGumbelGap) and of its
-//     logit, and lb rises to the largest lower bound of the wave;
-//  2. the tokens whose upper bound reaches lb join the wave's queue in LDS; a queue
-//     that would overflow is scored exactly, one token per lane, and at the end
-//     the four waves' queues are scored together.
+//     lb = min(m, bias(m)), and a token below reach_threshold(lb) stays under it;
+//     sampling: lb from m with the noise's overall minimum, and a vector none of whose
+//     tokens reaches lb even with the noise's overall maximum draws no noise (tested on
+//     its largest logit); the others draw their noise, each token's score is bounded from
+//     above by the bounds of its noise (noise_bits) and of its logit, and lb rises to
+//     the wave's largest lower bound;
+//  2. a vector whose largest bound reaches lb in some lane has its tokens tested one by
+//     one, and those that reach lb join the wave's queue in LDS; a queue that would
+//     overflow is scored exactly, one token per lane, and at the end the four waves'
+//     queues are scored together.
 // lb only rises.  A token left out scores below lb, which some token of the wave's
-// share attains, so the partial equals that of a full scan.  The sampling bounds
-// follow from monotone fp32 rounding: the score is (l * 1/T) + G with both steps
-// rounded and 1/T > 0.  Lanes see tokens out of index order, so their running
-// argmax breaks ties by index.
+// share attains, so the partial equals that of a full scan.  Lanes see tokens out of index
+// order, so their running argmax breaks ties by index.  Rows start anywhere, as in the
+// watermark.
+//
+// Sampling is bound by VALU issue: 38 instructions for the noise block of 4 tokens and about
+// 10 a token to bound it.  Testing vectors before tokens, the noise bound from the float's
+// bits (4 instructions, a gap of 0.17 instead of 0.84 between its bounds, so fewer tokens
+// queue) and the queue's count and the round keys in scalar registers took 256 x 152064
+// fp32 from 42.9 to 38 us (1100 -> 870 VALU instructions a wave), bf16 160 x 152064 from
+// 28.9 to 25.3.  Greedy reads at the memory's rate in large launches (bf16 900 x 152064:
+// 60.8 -> 47.4 us, 5.8 TB/s).  Rows off 16 bytes took an element-wise kernel before that
+// drew every token's colour: 48 x 128259, greedy bf16 self-salt width 4 / sampled fp32
+// context, 27.5 -> 7.9 us, 31.3 -> 12.8 us.
 template <typename T, int kSeeding, int kN, int kSub, int kW, bool kSample>
 __global__ void __launch_bounds__(kThreads)
 decode_vec_kernel(const T* __restrict__ logits, int64_t row_stride, uint32_t V, int64_t B,
                   const int32_t* __restrict__ context, int width, uint64_t key, uint32_t tm1,
                   int none_green, float delta, const uint64_t* __restrict__ seeds, float inv_t,
                   uint32_t segments, uint64_t* __restrict__ partials, uint32_t vbase) {
-  using VecT = typename std::conditional<sizeof(T) == 4, f32x4, u32x4>::type;
-  constexpr int kE = sizeof(T) == 4 ? 4 : 8;         // tokens per vector
-  const uint32_t jbase = vbase / kE;                 // vector index of the first column
+  using VecT = typename VecOf<T>::Value;
+  using MemT = typename VecOf<T>::Memory;
+  constexpr int kE = 16 / sizeof(T);                 // tokens per vector
+  const RowSplit sp = row_split<kE>(V, vbase);
+  const uint32_t jbase = sp.id;                      // the first vector's token id / kE
   __shared__ uint64_t lds_key[kThreads / 64], lds_part[kThreads / 64];
   // Per wave: token ids, then raw logits.  The queue is scored whenever it holds more
   // than 64 tokens before a vector is queued, so it never holds more than 64 plus one
@@ -1062,19 +1092,18 @@ decode_vec_kernel(const T* __restrict__ logits, int64_t row_stride, uint32_t V, 
   __shared__ uint32_t lds_count[kThreads / 64];
   uint32_t* q_v = lds_queue + (threadIdx.x / 64u) * 2u * kQueueCap;
   uint32_t* q_raw = q_v + kQueueCap;
-  constexpr uint32_t kPer = 16u / sizeof(T);
   constexpr uint32_t kSubVecs = kThreads * kN;       // vectors per sub-batch
-  const uint32_t full = V / kPer;
-  const uint32_t tail = V % kPer;
-  const uint32_t seg_base = blockIdx.x * (kSubVecs * kSub);
+  const uint32_t full = sp.full;
+  const uint32_t segment = blockIdx.x;
+  const uint32_t seg_base = segment * (kSubVecs * kSub);
   for (int64_t row = blockIdx.y; row < B; row += gridDim.y) {
     const T* row_ptr = logits + row * row_stride;
-    const VecT* vec = reinterpret_cast<const VecT*>(row_ptr);
+    const MemT* vec = reinterpret_cast<const MemT*>(row_ptr + sp.head);
     Score<kSample> sc{0u, inv_t};
     RoundKeys nk{};
     if constexpr (kSample) {
       sc.seed = seeds[row];
-      nk = vector_round_keys(key_of(sc.seed));
+      nk = scalar_round_keys(key_of(sc.seed));
     }
     const RowSeed<kW> rs = row_seed<kSeeding, kW>(key, context + row * width, width);
     const float dt = fabsf(delta) * inv_t;
@@ -1082,6 +1111,19 @@ decode_vec_kernel(const T* __restrict__ logits, int64_t row_stride, uint32_t V, 
     LaneBest best = lane_best_init();
     float lb = -INFINITY;           // the best score is at least lb (the same in every lane)
     uint32_t queued = 0;            // tokens in the wave's queue (the same in every lane)
+    // The columns outside whole vectors (at most 14) are queued by the first wave of the
+    // last segment, which has the fewest vectors and is never empty.  (Scored on their own
+    // they cost 4 VGPRs a lane and with them a wave per SIMD: sampling 256 x 152064 fp32
+    // 43.9 -> 50.2 us.)
+    if (sp.edges() != 0u && segment + 1u == segments &&
+        __builtin_amdgcn_readfirstlane(threadIdx.x / 64u) == 0u) {
+      if (threadIdx.x < sp.edges()) {
+        const uint32_t c = sp.template edge<kE>(threadIdx.x);   // column; the token id is vbase + c
+        q_v[threadIdx.x] = vbase + c;
+        q_raw[threadIdx.x] = raw_bits(row_ptr[c]);
+      }
+      queued = sp.edges();
+    }
     // Sub-batch `sub` into registers; the next one is loaded while this one is scored.
     auto load_sub = [&](VecT (&buf)[kN], int sub) {
       // Opaque to the optimiser, so that no Philox work is hoisted out of the loops.
@@ -1094,7 +1136,7 @@ decode_vec_kernel(const T* __restrict__ logits, int64_t row_stride, uint32_t V, 
 #pragma unroll
         for (int n = 0; n < kN; ++n) {
           const uint32_t j = sub_first + n * kThreads + threadIdx.x;
-          buf[n] = VecT{};
+          buf[n] = lowest_vec(VecT{});
           if (j < full) buf[n] = stream_load(vec + j);
         }
       }
@@ -1107,83 +1149,75 @@ decode_vec_kernel(const T* __restrict__ logits, int64_t row_stride, uint32_t V, 
       asm volatile("" : "+s"(id_first));
       const bool whole = sub_first + kSubVecs <= full;
       float m = -INFINITY;
-#pragma unroll
-      for (int n = 0; n < kN; ++n)
-        if (whole || sub_first + n * kThreads + threadIdx.x < full) m = fold_max(buf[n], m);
-      float hi[kN][kE];
-      if constexpr (!kSample) {
-        // Greedy decoding: the largest logit's own value bounds the best from below,
-        // and a token's larger candidate value bounds it from above.
-        lb = fmaxf(lb, reach_bound(wave_max(m), delta, T{}));
-#pragma unroll
-        for (int n = 0; n < kN; ++n) upper_logits(buf[n], delta, dplus, hi[n]);
-      } else {
-      const float lb0 = fmaxf(lb, reach_bound(wave_max(m), delta, T{}) * inv_t + kGumbelLo);
-      float top = -INFINITY;    // the lane's largest hi among tokens whose draw has c >= 2
+      float vm[kN];                   // each vector's largest logit, NaN when it has one
 #pragma unroll
       for (int n = 0; n < kN; ++n) {
-        const uint32_t j = sub_first + n * kThreads + threadIdx.x;
-        float phi[kE];
-        upper_logits(buf[n], delta, dplus, inv_t, phi);
-        float vmax = -INFINITY;   // NaN-propagating: a NaN token is always kept
+        vm[n] = vec_max(buf[n]);
+        m = max_raw(m, vm[n]);
+      }
+      float hi[kSample ? kN : 1][kE]; // sampling: the tokens' upper bounds, noise_bits apart
+      float reach;                    // what a token's bound has to reach (the same in every lane)
+      if constexpr (!kSample) {
+        lb = fmaxf(lb, reach_bound(wave_max(m), delta, T{}));
+        reach = reach_threshold(lb, dplus, T{});
+      } else {
+        const float lb0 = fmaxf(lb, reach_bound(wave_max(m), delta, T{}) * inv_t + kGumbelLo);
+        float top = -INFINITY;        // the lane's largest hi
 #pragma unroll
-        for (int e = 0; e < kE; ++e) vmax = __builtin_elementwise_maximum(vmax, phi[e]);
-        const bool reach = (whole || j < full) && !(vmax + kGumbelHi < lb0);
+        for (int n = 0; n < kN; ++n) {
+          const float most = upper_logit(vm[n], dplus, T{}) * inv_t + kGumbelHi;
+          vm[n] = -INFINITY;          // from here on the vector's largest hi
 #pragma unroll
-        for (int e = 0; e < kE; ++e) hi[n][e] = -INFINITY;
-        if (reach) {
-          uint32_t nw[kE];
-          noise_words(id_first + n * kThreads + threadIdx.x, nk, nw);
+          for (int e = 0; e < kE; ++e) asm("" : "=v"(hi[n][e]));   // any value: vm decides
+          if (!(most < lb0)) {
+            const uint32_t j = id_first + n * kThreads + threadIdx.x;
+            uint32_t nw[kE];
+            noise_words(j, nk, nw);
+            upper_logits(buf[n], dplus, hi[n]);
 #pragma unroll
-          for (int e = 0; e < kE; ++e) {
-            const float c = noise_ones(nw[e]);
-            hi[n][e] = phi[e] + gumbel_upper(c);
-            top = fmaxf(top, c >= 2.0f ? hi[n][e] : -INFINITY);
+            for (int e = 0; e < kE; ++e)
+              hi[n][e] = __builtin_fmaf(noise_bits(nw[e]), -kNoiseBitsScale, hi[n][e] * inv_t);
+            vm[n] = vec_max(hi[n]);
+            top = max_raw(top, vm[n]);
           }
         }
-      }
-      // A token with c >= 2 and upper bound hi scores at least hi - gap - d: its noise
-      // is at least gumbel_upper(c) - kGumbelGap, and its two candidate logits times
-      // 1/T differ by at most |delta|/T plus roundings (of the bias, to 8 significant
-      // bits for bf16, and of the products), which the relative term covers, as it
-      // covers the rounding of this subtraction.  An infinite top gives no bound.
-      {
+        // The lane's token with the largest bound `up`, if its noise lies in the upper
+        // range (as it must when `up` exceeds every logit of the lane by more than the
+        // noise bound outside that range), scores at least up - gap - d: its noise is that
+        // close to its bound, and its two candidate logits times 1/T differ by at most
+        // |delta|/T plus roundings (of the bias, to 8 significant bits for bf16, of the
+        // products and of these sums), which the relative term covers.  An infinite
+        // `up` gives no bound.
         constexpr float kRel = sizeof(T) == 4 ? 0x1p-18f : 0x1p-7f;
-        const float slack = kGumbelGap + dt + kRel * (fabsf(top) + 18.0f + dt);
-        const float lb_lane = top < INFINITY ? top - slack : -INFINITY;
+        const float up = top + kNoiseBitsOffset;
+        const float pm = upper_logit(m, dplus, T{}) * inv_t;
+        const float slack = kNoiseGap + dt + kRel * (fabsf(up) + 18.0f + dt);
+        const bool upper_range = up - pm > kNoiseUpperRange + 0x1p-18f * (fabsf(pm) + 18.0f);
+        const float lb_lane = up < INFINITY && upper_range ? up - slack : -INFINITY;
         lb = fmaxf(lb0, wave_max(lb_lane));
-      }
+        // a score of at least lb needs a bound of at least this (the roundings of hi)
+        reach = (lb - kNoiseBitsOffset) - 0x1p-20f * (fabsf(lb) + 256.0f);
       }
 
       // Queue the tokens whose upper bound reaches lb.  The counters are the same in
       // every lane.
 #pragma unroll
       for (int n = 0; n < kN; ++n) {
+        const uint32_t j = sub_first + n * kThreads + threadIdx.x;
+        uint64_t lanes = __ballot(!(vm[n] < reach));
+        if (!whole) lanes &= __ballot(j < full);
+        if (lanes == 0u) continue;
         if (queued > 64u) {
           score_queue<T, kSeeding, kW, kSample>(best, q_v, q_raw, queued, rs, tm1, none_green, delta, sc);
           queued = 0;
-          lb = fmaxf(lb, wave_max(best.any ? best.v : -INFINITY));
         }
-        const uint32_t j = sub_first + n * kThreads + threadIdx.x;
         const uint32_t jid = id_first + n * kThreads + threadIdx.x;
-        if (whole) {
 #pragma unroll
-          for (int e = 0; e < kE; ++e) {
-            const bool reaches = !(hi[n][e] < lb);
-            const uint64_t mask = __ballot(reaches);
-            if (reaches) enqueue(q_v, q_raw, queued, mask, jid * kE + e, raw_elem(buf[n], e));
-            queued = __builtin_amdgcn_readfirstlane(queued + static_cast<uint32_t>(__popcll(mask)));
-          }
-        } else {
-          const bool valid = j < full;
-          const uint64_t valid_mask = __ballot(valid);
-#pragma unroll
-          for (int e = 0; e < kE; ++e) {
-            const bool reaches = !(hi[n][e] < lb);
-            const uint64_t mask = __ballot(reaches) & valid_mask;
-            if (valid && reaches) enqueue(q_v, q_raw, queued, mask, jid * kE + e, raw_elem(buf[n], e));
-            queued = __builtin_amdgcn_readfirstlane(queued + static_cast<uint32_t>(__popcll(mask)));
-          }
+        for (int e = 0; e < kE; ++e) {
+          const uint64_t mask = __ballot(!((kSample ? hi[n][e] : elem(buf[n], e)) < reach)) & lanes;
+          if (__builtin_amdgcn_inverse_ballot_w64(mask))
+            enqueue(q_v, q_raw, queued, mask, jid * kE + e, raw_elem(buf[n], e));
+          queued += static_cast<uint32_t>(__popcll(mask));
         }
       }
     };
@@ -1219,44 +1253,7 @@ decode_vec_kernel(const T* __restrict__ logits, int64_t row_stride, uint32_t V, 
                                                delta, sc);
       }
     }
-    // The row's partial last vector, element by element, by lane 0 of the segment
-    // that holds it.
-    if (tail != 0u && threadIdx.x == 0 && full >= seg_base && full - seg_base < kSubVecs * kSub) {
-      for (uint32_t e = 0; e < tail; ++e) {
-        const uint32_t c = full * kPer + e;          // column; the token id is vbase + c
-        const uint32_t v = vbase + c;
-        const bool g = !none_green && is_green(draw<kSeeding>(rs, v), tm1);
-        consider_any_order(best, sc.of(widen(bias_elem(row_ptr[c], delta, g)), v), v);
-      }
-    }
-    block_argmax_store(best, partials + row * segments + blockIdx.x, lds_key, lds_part);
-  }
-}
-
-// Rows that are not 16-byte aligned: one element per thread per step, a segment of
-// kArgmaxSegElems elements per workgroup.
-template <typename T, int kSeeding, int kW, bool kSample>
-__global__ void __launch_bounds__(kThreads)
-argmax_elem_kernel(const T* __restrict__ logits, int64_t row_stride, uint32_t V, int64_t B,
-                   const int32_t* __restrict__ context, int width, uint64_t key, uint32_t tm1,
-                   int none_green, float delta, const uint64_t* __restrict__ seeds, float inv_t,
-                   uint32_t segments, uint64_t* __restrict__ partials, uint32_t vbase) {
-  __shared__ uint64_t lds_key[kThreads / 64], lds_part[kThreads / 64];
-  const uint64_t seg_first = static_cast<uint64_t>(blockIdx.x) * kArgmaxSegElems;
-  for (int64_t row = blockIdx.y; row < B; row += gridDim.y) {
-    const RowSeed<kW> rs = row_seed<kSeeding, kW>(key, context + row * width, width);
-    const Score<kSample> sc{kSample ? seeds[row] : 0u, inv_t};
-    LaneBest lb = lane_best_init();
-    for (int s = 0; s < kElemSegSteps; ++s) {
-      const uint64_t v64 = seg_first + static_cast<uint64_t>(s) * kThreads + threadIdx.x;
-      if (v64 < V) {
-        const uint32_t c = static_cast<uint32_t>(v64);   // column; the token id is vbase + c
-        const uint32_t v = vbase + c;
-        const bool g = !none_green && is_green(draw<kSeeding>(rs, v), tm1);
-        consider(lb, sc.of(widen(bias_elem(logits[row * row_stride + c], delta, g)), v), v);
-      }
-    }
-    block_argmax_store(lb, partials + row * segments + blockIdx.x, lds_key, lds_part);
+    block_argmax_store(best, partials + row * segments + segment, lds_key, lds_part);
   }
 }
 
@@ -1917,12 +1914,14 @@ void dispatch_candidates(void* logits, int64_t B, uint32_t V, int64_t row_stride
                        p, row_stride, V, B, cand, k, context, width, key, tm1, delta);
 }
 
-// Segments per row of the fused decoding: vector path and element path.
+// Vectors per lane (and so segments per row) of the fused decoding.
 template <typename T>
 constexpr int decode_vecs_for(bool sample) {
   return sizeof(T) == 4 ? (sample ? SBW_DECODE_VECS_F32 : SBW_DECODE_VECS_F32_GREEDY)
                         : (sample ? SBW_DECODE_VECS_BF16_SAMPLE : SBW_DECODE_VECS_BF16);
 }
+template <typename T>
+constexpr int decode_subs_for(bool sample) { return sizeof(T) == 2 && !sample ? SBW_DECODE_SUBS_BF16 : 1; }
 template <typename T>
 constexpr uint64_t vec_segment_elems(int kN) { return (16u / sizeof(T)) * kThreads * kN; }
 // Small grids: a launch of fewer workgroups than this takes half the vectors per lane
@@ -1931,12 +1930,12 @@ constexpr uint64_t vec_segment_elems(int kN) { return (16u / sizeof(T)) * kThrea
 // workgroups instead of 768 (about 8 % faster); B = 64 rows of 152064 (960-1600
 // workgroups) stay.
 constexpr int64_t kSmallDecodeGrid = 900;
-// The workspace is sized for the element path; vector segments must be at least as long.
+// The workspace is sized for segments of kArgmaxSegElems; none may be shorter.
 static_assert(vec_segment_elems<float>(SBW_DECODE_VECS_F32 / 2) >= kArgmaxSegElems &&
                   vec_segment_elems<float>(SBW_DECODE_VECS_F32_GREEDY / 2) >= kArgmaxSegElems &&
-                  vec_segment_elems<uint16_t>(SBW_DECODE_VECS_BF16 / 2) >= kArgmaxSegElems &&
+                  vec_segment_elems<uint16_t>(SBW_DECODE_VECS_BF16 / 2) * SBW_DECODE_SUBS_BF16 >= kArgmaxSegElems &&
                   vec_segment_elems<uint16_t>(SBW_DECODE_VECS_BF16_SAMPLE / 2) >= kArgmaxSegElems,
-              "vector segments must not outnumber element segments");
+              "the segments of a row must fit its part of the workspace");
 
 // The per-row noise seeds and 1/T of a sampling pass (unused by greedy decoding).
 struct SampleArgs {
@@ -1947,36 +1946,29 @@ struct SampleArgs {
 template <typename T, int kSeeding, int kW, bool kSample>
 void launch_argmax(const void* logits, int64_t B, uint32_t V, int64_t row_stride,
                    const int32_t* context, int width, uint64_t key, uint32_t tm1, int none,
-                   float delta, const SampleArgs& sa, uint32_t vbase, bool aligned, int32_t* tokens,
-                   float* values, uint64_t* partials, hipStream_t stream) {
+                   float delta, const SampleArgs& sa, uint32_t vbase, int32_t* tokens, float* values,
+                   uint64_t* partials, hipStream_t stream) {
   const T* p = static_cast<const T*>(logits);
   const uint32_t rows = static_cast<uint32_t>(B < kMaxGridY ? B : kMaxGridY);
+  constexpr int kN = decode_vecs_for<T>(kSample);
+  constexpr int kNs = kN / 2;
+  constexpr int kSub = decode_subs_for<T>(kSample);
+  const bool crowded = sizeof(T) == 4 && !kSample &&
+                       B * static_cast<int64_t>(V) * 4 >= SBW_XCD_ROWS_MIN_BYTES;
+  const uint32_t spare_lds = crowded ? kCrowdedLds : 0u;
+  auto launch = [&](auto vecs, uint64_t seg) {
+    const uint32_t segments = static_cast<uint32_t>((uint64_t{V} + seg - 1) / seg);
+    hipLaunchKernelGGL((decode_vec_kernel<T, kSeeding, decltype(vecs)::value, kSub, kW, kSample>),
+                       dim3(segments, rows), dim3(kThreads), spare_lds, stream, p, row_stride, V, B, context,
+                       width, key, tm1, none, delta, sa.seeds, sa.inv_t, segments, partials, vbase);
+    return segments;
+  };
+  const uint64_t seg = vec_segment_elems<T>(kN) * kSub;
   uint32_t segments;
-  if (aligned) {
-    constexpr int kN = decode_vecs_for<T>(kSample);
-    constexpr int kNs = kN / 2;
-    const uint64_t seg = vec_segment_elems<T>(kN) * SBW_DECODE_SUBS;
-    segments = static_cast<uint32_t>((static_cast<uint64_t>(V) + seg - 1) / seg);
-    if (int64_t{segments} * rows >= kSmallDecodeGrid) {
-      hipLaunchKernelGGL((decode_vec_kernel<T, kSeeding, kN, SBW_DECODE_SUBS, kW, kSample>),
-                         dim3(segments, rows), dim3(kThreads), 0, stream, p, row_stride, V, B,
-                         context, width, key, tm1, none, delta, sa.seeds, sa.inv_t, segments,
-                         partials, vbase);
-    } else {
-      const uint64_t seg_s = vec_segment_elems<T>(kNs) * SBW_DECODE_SUBS;
-      segments = static_cast<uint32_t>((static_cast<uint64_t>(V) + seg_s - 1) / seg_s);
-      hipLaunchKernelGGL((decode_vec_kernel<T, kSeeding, kNs, SBW_DECODE_SUBS, kW, kSample>),
-                         dim3(segments, rows), dim3(kThreads), 0, stream, p, row_stride, V, B,
-                         context, width, key, tm1, none, delta, sa.seeds, sa.inv_t, segments,
-                         partials, vbase);
-    }
-  } else {
-    segments = static_cast<uint32_t>((static_cast<uint64_t>(V) + kArgmaxSegElems - 1) /
-                                     kArgmaxSegElems);
-    hipLaunchKernelGGL((argmax_elem_kernel<T, kSeeding, kW, kSample>), dim3(segments, rows),
-                       dim3(kThreads), 0, stream, p, row_stride, V, B, context, width, key, tm1,
-                       none, delta, sa.seeds, sa.inv_t, segments, partials, vbase);
-  }
+  if ((V + static_cast<int64_t>(seg) - 1) / static_cast<int64_t>(seg) * rows >= kSmallDecodeGrid)
+    segments = launch(std::integral_constant<int, kN>{}, seg);
+  else
+    segments = launch(std::integral_constant<int, kNs>{}, vec_segment_elems<T>(kNs) * kSub);
   const int64_t row_blocks = grid_for((B + kThreads / 64 - 1) / (kThreads / 64));
   hipLaunchKernelGGL(argmax_finish_kernel, dim3(row_blocks), dim3(kThreads), 0, stream, partials,
                      segments, B, tokens, values);
@@ -1986,23 +1978,23 @@ template <typename T, bool kSample>
 void dispatch_argmax(const void* logits, int64_t B, uint32_t V, int64_t row_stride,
                      const int32_t* context, int width, uint64_t key, uint32_t tm1, int none,
                      float delta, const SampleArgs& sa, sbw_seeding_t seeding, uint32_t vbase,
-                     bool aligned, int32_t* tokens, float* values, uint64_t* partials,
+                     int32_t* tokens, float* values, uint64_t* partials,
                      hipStream_t st) {
   if (seeding == SBW_SEED_CONTEXT)
     launch_argmax<T, kContext, kMaxWidth, kSample>(logits, B, V, row_stride, context, width, key,
-                                                   tm1, none, delta, sa, vbase, aligned, tokens,
+                                                   tm1, none, delta, sa, vbase, tokens,
                                                    values, partials, st);
   else if (width == 1)
     launch_argmax<T, kSelfSalt, 1, kSample>(logits, B, V, row_stride, context, width, key, tm1,
-                                            none, delta, sa, vbase, aligned, tokens, values,
+                                            none, delta, sa, vbase, tokens, values,
                                             partials, st);
   else if (width <= kMidWidth)
     launch_argmax<T, kSelfSalt, kMidWidth, kSample>(logits, B, V, row_stride, context, width, key,
-                                                    tm1, none, delta, sa, vbase, aligned, tokens,
+                                                    tm1, none, delta, sa, vbase, tokens,
                                                     values, partials, st);
   else
     launch_argmax<T, kSelfSalt, kMaxWidth, kSample>(logits, B, V, row_stride, context, width, key,
-                                                    tm1, none, delta, sa, vbase, aligned, tokens,
+                                                    tm1, none, delta, sa, vbase, tokens,
                                                     values, partials, st);
 }
 
@@ -2159,15 +2151,6 @@ bool ids_fit(int64_t V, int64_t v_offset) {
   return V < kMaxTokenIds && v_offset <= kMaxTokenIds - V;
 }
 
-// The vector kernels load 16 bytes per lane and draw whole Philox blocks: rows must
-// start on 16 bytes, and the shard's first token id must sit at the start of a vector
-// (a multiple of 4 for fp32, of 8 for bf16).  Anything else takes the element path.
-bool vector_path_ok(const void* logits, int64_t row_stride, sbw_dtype_t dtype, uint32_t vbase) {
-  const uint32_t esize = dtype == SBW_F32 ? 4u : 2u;
-  return reinterpret_cast<uintptr_t>(logits) % 16 == 0 &&
-         (static_cast<uint64_t>(row_stride) * esize) % 16 == 0 && vbase % (16u / esize) == 0;
-}
-
 // ---------------------------------------------------------------------------
 // Scratch of sbw_watermark_argmax_noalloc: the per-segment partials that the other
 // decoding calls keep in the caller's workspace, in an array of the code object, one
@@ -2253,16 +2236,15 @@ sbw_status_t decode_impl(const void* logits, sbw_dtype_t dtype, int64_t B, int64
   const uint32_t tm1 = none ? 0u : static_cast<uint32_t>(T - 1);
   const float d = delta;
   const uint32_t vbase = static_cast<uint32_t>(v_offset);
-  const bool aligned = vector_path_ok(logits, row_stride, dtype, vbase);
   const uint32_t v32 = static_cast<uint32_t>(V);
   const int w = static_cast<int>(width);
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (dtype == SBW_F32)
     dispatch_argmax<float, kSample>(logits, B, v32, row_stride, context, w, key, tm1, none, d, sa,
-                                    seeding, vbase, aligned, tokens, values, workspace, st);
+                                    seeding, vbase, tokens, values, workspace, st);
   else
     dispatch_argmax<uint16_t, kSample>(logits, B, v32, row_stride, context, w, key, tm1, none, d,
-                                       sa, seeding, vbase, aligned, tokens, values, workspace, st);
+                                       sa, seeding, vbase, tokens, values, workspace, st);
   return after_launch();
 }
 

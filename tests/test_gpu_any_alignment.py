@@ -81,3 +81,38 @@ def test_bf16_slab_from_its_line(env):
 def test_context_whole_rows_per_xcd_with_edges(env, dtype):
     """Launches large enough for whole rows per XCD, whose rows have single columns."""
     check(env, dtype, "context", 4, 512 if dtype == "f32" else 1024, 3, 131079)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("sample", [False, True])
+@pytest.mark.parametrize("B,start,n,pad", [(3, 1, 1, 0), (5, 3, 4, 1), (4, 5, 15, 0), (3, 7, 4096, 3),
+                                           (2, 2, 12290, 1), (200, 1003, 40969, 2)])
+def test_decode_from_any_column(env, dtype, sample, B, start, n, pad):
+    """Greedy decoding and sampling of a shard: token and value bit for bit, with the row's
+    winner in turn before, inside and after its whole vectors."""
+    torch, sbw, dev = env
+    rng = np.random.default_rng(B + start + n)
+    x = special_logits(rng, B, start + n, "f32")
+    x[~np.isfinite(x)] = 0.0
+    for b in range(B):
+        x[b, start + [0, n - 1, n // 2][b % 3]] = 1e4
+    full = workloads.f32_to_bf16_bits(x) if dtype == "bf16" else x
+    shard = np.zeros((B, n + pad), dtype=full.dtype)
+    shard[:, :n] = full[:, start:]
+    ctx = workloads.context_tokens(B, 2, start + n, rng)
+    seeds = rng.integers(0, 2**63, B, dtype=np.int64)
+    hidden = full.copy()      # the whole row with the columns before the shard out of the running
+    hidden[:, :start] = workloads.f32_to_bf16_bits(np.float32([-1e30]))[0] if dtype == "bf16" else -1e30
+    t = _to_device(torch, dev, shard)[:, :n]
+    c = torch.from_numpy(np.ascontiguousarray(ctx, dtype=np.int32)).to(dev)
+    for seeding in ("context", "self_salt"):
+        say(f"decode from any column {dtype} {seeding} sample={sample} B={B} start={start} n={n} pad={pad}")
+        if sample:
+            got = sbw.watermark_sample(t, c, WIDE, 0.25, 2.0, torch.from_numpy(seeds).to(dev), seeding, 0.7,
+                                       v_offset=start)
+            expect = oracle.watermark_sample(hidden, ctx, WIDE, 0.25, 2.0, seeding, seeds.view(np.uint64), 0.7)
+        else:
+            got = sbw.watermark_argmax(t, c, WIDE, 0.25, 2.0, seeding, v_offset=start)
+            expect = oracle.watermark_argmax(hidden, ctx, WIDE, 0.25, 2.0, seeding)
+        assert np.array_equal(got[0].cpu().numpy(), expect[0])
+        assert np.array_equal(got[1].cpu().numpy().view(np.uint32), expect[1].view(np.uint32))

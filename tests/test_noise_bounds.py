@@ -78,3 +78,17 @@ def test_overall_range(every_draw):
     _, g = every_draw
     k = header_constants()
     assert k["kGumbelLo"] < g.min() and g.max() < k["kGumbelHi"]
+
+
+def test_bounds_from_the_bits_of_the_tail_probability(every_draw):
+    """The finer form that the kernels evaluate, with any low bits of the draw."""
+    x, g = every_draw
+    k = header_constants()
+    for low in (0, 0x1A5, 0x1FF):
+        y = (~(x | np.uint32(low)) & np.uint32(0xFFFFFE00)) | np.uint32(0x100)
+        bits = y.astype(np.float32).view(np.uint32).astype(np.float32).astype(np.float64)
+        upper = np.float64(k["kNoiseBitsOffset"]) - np.float64(k["kNoiseBitsScale"]) * bits
+        assert (upper - g).min() > 0.0005                    # room for the fp32 logarithm and fma
+        tail = upper > np.float64(k["kNoiseUpperRange"])
+        assert np.all(y[tail] < 1 << 30)                     # q < 1/4 wherever the bound is that large
+        assert (upper - g)[tail].max() < np.float64(k["kNoiseGap"]) - 0.003
