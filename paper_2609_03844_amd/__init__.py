@@ -1,7 +1,8 @@
 """Stateless Bernoulli Watermarking on MI355X (gfx950): Python binding of libsbw.
 
-A thin ctypes layer over the C ABI in ``include/sbw.h``; it only marshals
-arguments (device pointers, sizes, the current HIP stream).  Every step of the
+A thin layer over the C ABI in ``include/sbw.h``; it only marshals arguments (device
+pointers, sizes, the current HIP stream): in native code (``_binding.so``) for ordinary
+calls, by ctypes with every check spelled out for the others.  Every step of the
 watermark and detect path runs in the HIP kernels of ``libsbw.so``.  There is no
 fallback: if the library is missing this module raises on import.
 
@@ -128,6 +129,7 @@ def _load() -> ctypes.CDLL:
 
 
 _lib = _load()
+from . import _binding as _native  # noqa: E402  (linked against libsbw.so)
 
 
 def library_path() -> str:
@@ -219,6 +221,11 @@ def watermark(logits: torch.Tensor, prev_tokens: torch.Tensor, key: int, gamma: 
     or int32 [B, h] (the h tokens before the step, context width h <= 8).  v_offset:
     the token id of column 0 when the logits are one shard of the vocabulary.
     """
+    if stream is None:
+        status = _native.watermark(logits, prev_tokens, key, gamma, delta, seeding, v_offset)
+        if status is not None:
+            _check(status)
+            return logits
     if logits.dim() != 2:
         raise ValueError("logits must be [B, V]")
     if logits.dtype == torch.float32:
@@ -251,6 +258,12 @@ def watermark_candidates(logits: torch.Tensor, prev_tokens: torch.Tensor,
     """The watermark restricted to candidates [B, k] int32 (k <= 1024), in place; the
     top-k self-salt scheme (SBW-ss) with its top-k ids as candidates.  Ids outside
     [0, V) are ignored, a repeated id is biased once; returns ``logits``."""
+    if stream is None:
+        status = _native.watermark_candidates(logits, prev_tokens, candidates, key, gamma, delta,
+                                              seeding)
+        if status is not None:
+            _check(status)
+            return logits
     if logits.dim() != 2:
         raise ValueError("logits must be [B, V]")
     if logits.dtype == torch.float32:
@@ -285,6 +298,11 @@ def watermark_argmax(logits: torch.Tensor, prev_tokens: torch.Tensor, key: int, 
     scratch tensor of at least argmax_workspace_size(B, V) elements (allocated here
     when not given).  With v_offset the logits are a vocabulary shard and the tokens
     global ids."""
+    if stream is None:
+        out = _native.decode(logits, prev_tokens, key, gamma, delta, seeding, None, 1.0, tokens,
+                             values, workspace, with_values, v_offset)
+        if out is not None:
+            return out if type(out) is tuple else _check(out)
     if logits.dim() != 2:
         raise ValueError("logits must be [B, V]")
     if logits.dtype == torch.float32:
@@ -381,6 +399,11 @@ def watermark_sample(logits: torch.Tensor, prev_tokens: torch.Tensor, key: int, 
     (Gumbel-max with noise from seeds, uint64 [B] as an int64 tensor).  Returns (tokens
     int32 [B], scores float32 [B] or None); the workspace and v_offset are as for
     watermark_argmax."""
+    if stream is None and seeds is not None:
+        out = _native.decode(logits, prev_tokens, key, gamma, delta, seeding, seeds,
+                             inv_temperature, tokens, scores, workspace, with_scores, v_offset)
+        if out is not None:
+            return out if type(out) is tuple else _check(out)
     if logits.dim() != 2:
         raise ValueError("logits must be [B, V]")
     if logits.dtype == torch.float32:
@@ -484,6 +507,10 @@ def detect(tokens: torch.Tensor, key: int, gamma: float, seeding="context",
            width: int = 1):
     """Green count and z-score per sequence of tokens [N, L] int32 (unit stride along L).
     Positions width..L-1 are scored under the `width` tokens before each (T = L - width)."""
+    if stream is None:
+        out = _native.detect(tokens, key, gamma, seeding, width, None, False, counts, False, z)
+        if out is not None:
+            return out if type(out) is tuple else _check(out)
     if tokens.dtype != torch.int32 or tokens.dim() != 2:
         raise ValueError("tokens must be int32 [N, L]")
     N, L = tokens.shape
@@ -514,6 +541,11 @@ def detect_ex(tokens: torch.Tensor, key: int, gamma: float, seeding="context", w
     lengths int32 [N] or None (clamped to [0, L]); with ignore_repeated, each distinct
     (width+1)-gram of a text is scored once (L - width <= 4096).  Returns (green
     counts int32 [N], scored positions int32 [N], z float64 [N])."""
+    if stream is None:
+        out = _native.detect(tokens, key, gamma, seeding, width, lengths, ignore_repeated, counts,
+                             scored, z)
+        if out is not None:
+            return out if type(out) is tuple else _check(out)
     if tokens.dtype != torch.int32 or tokens.dim() != 2:
         raise ValueError("tokens must be int32 [N, L]")
     N, L = tokens.shape

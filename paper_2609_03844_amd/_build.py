@@ -1,9 +1,12 @@
-"""Builds libsbw.so in-tree with hipcc for gfx950, and libsbw_rate.so, the Philox
-throughput probe that only the benchmark loads (not part of the ABI)."""
+"""Builds libsbw.so in-tree with hipcc for gfx950, _binding.so, the Python entry points'
+native call path, and libsbw_rate.so, the Philox throughput probe that only the benchmark
+loads (neither is part of the ABI)."""
 from __future__ import annotations
 
+import importlib.util
 import os
 import subprocess
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -11,6 +14,8 @@ CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIBRARY = os.path.join(PKG, "libsbw.so")
 SOURCES = [os.path.join(CSRC, "sbw_kernels.hip")]
+BINDING = os.path.join(PKG, "_binding.so")
+BINDING_SOURCE = os.path.join(CSRC, "binding.cpp")
 RATE_LIBRARY = os.path.join(PKG, "libsbw_rate.so")
 RATE_SOURCES = [os.path.join(CSRC, "philox_rate.hip")]
 HEADERS = [os.path.join(CSRC, "sbw_device.hpp"), os.path.join(INCLUDE, "sbw.h")]
@@ -54,6 +59,23 @@ def build_rate() -> str:
     return build(output=RATE_LIBRARY, sources=RATE_SOURCES)
 
 
+def build_binding() -> str:
+    """The CPython extension, host code only, against torch's headers and libsbw.so."""
+    torch = os.path.dirname(importlib.util.find_spec("torch").origin)
+    lib = os.path.join(torch, "lib")
+    include = os.path.join(torch, "include")
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+           "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", "-I", INCLUDE, "-isystem", include,
+           "-isystem", os.path.join(include, "torch", "csrc", "api", "include"),
+           "-isystem", "/opt/rocm/include", "-isystem", sysconfig.get_paths()["include"],
+           BINDING_SOURCE, "-o", BINDING + ".tmp", "-L", PKG, "-lsbw", "-L", lib, "-ltorch_python",
+           "-ltorch_cpu", "-lc10", "-lc10_hip", "-Wl,-rpath,$ORIGIN", "-Wl,-rpath," + lib]
+    subprocess.run(cmd, check=True)
+    os.replace(BINDING + ".tmp", BINDING)
+    return BINDING
+
+
 if __name__ == "__main__":
     print(build())
+    print(build_binding())
     print(build_rate())
