@@ -1648,91 +1648,121 @@ __global__ void __launch_bounds__(kThreads) detect_zero_kernel(uint64_t* __restr
 // A lane claims an empty slot with a compare-and-swap, or meets a slot holding an
 // equal n-gram and stops there, so exactly one position of every distinct n-gram is
 // claimed and scored, whatever the interleaving; the tokens are compared only when
-// the hash bits agree.
+// the hash bits agree.  A position's latency, the chain from hash over probes to draw, bounds
+// it, so few texts take many threads (unique_block) and a lane's token is loaded again while
+// it probes; two or four positions probed at once per lane measured slower (1024 x 1024:
+// 10.4 us with one, 11.1, 12.5).
 constexpr uint32_t kMaxUniqueSlots = 8192;   // 32 KB of LDS (+ up to 16 KB of tokens): 4096 positions
 constexpr uint32_t kSlotPosBits = 13;        // positions < 8192 (L <= 4096 + kMaxWidth)
 constexpr int32_t kEmptySlot = -1;           // never a slot value: no position is 8191
 static_assert(kMaxUniqueSlots / 2 + kMaxWidth < (1u << kSlotPosBits) - 1u,
               "every position fits the slot's position bits and differs from 8191");
 
-__device__ __forceinline__ uint32_t ngram_hash(const int32_t* seq, int64_t i, int width) {
-  uint32_t h = 0x9E3779B9u;
+// Self-salt stages J(token) instead of the token: J is a bijection of 32-bit words (each of
+// its steps is), so equal n-grams are those of equal J, and no position hashes its window
+// again.  `seq` below holds J(token) (self-salt) or the token (context).
+__device__ __forceinline__ uint32_t ngram_hash(const uint32_t* last, int width) {
+  // a sum of products with odd constants, then mixed downwards for the slot's low bits
+  uint32_t h = 0u, m = 0x9E3779B1u;
   for (int k = 0; k <= width; ++k) {
-    h = (h ^ static_cast<uint32_t>(seq[i - width + k])) * 0x85EBCA6Bu;
-    h ^= h >> 13;
+    h += last[-k] * m;
+    m *= 0x85EBCA6Bu;
   }
+  h ^= h >> 15;
+  h *= 0x2C1B3C6Du;
   return h ^ (h >> 16);
 }
 
-__device__ __forceinline__ bool same_ngram(const int32_t* seq, int64_t a, int64_t b, int width) {
+__device__ __forceinline__ bool same_ngram(const uint32_t* a, const uint32_t* b, int width) {
   bool same = true;
-  for (int k = 0; k <= width; ++k) same = same && seq[a - width + k] == seq[b - width + k];
+  for (int k = 0; k <= width; ++k) same = same && a[-k] == b[-k];
   return same;
 }
 
-#ifndef SBW_UNIQUE_BLOCK
-#define SBW_UNIQUE_BLOCK 256  // threads per sequence of the repeat-rule detect
-#endif
-constexpr int kUniqueBlock = SBW_UNIQUE_BLOCK;
-
+// Membership of token v, whose staged value is *last, under the window before it.
 template <int kSeeding, int kW>
-__global__ void __launch_bounds__(kUniqueBlock)
+__device__ __forceinline__ bool staged_green(uint64_t key, const uint32_t* last, int width, uint32_t v,
+                                             uint32_t tm1) {
+  uint64_t r;
+  if (kSeeding == kContext) {
+    uint64_t sum = 0u;
+#pragma unroll
+    for (int k = 1; k <= kW; ++k)
+      if (kW == 1 || k <= width) sum += last[-k];
+    r = kW == 1 ? lane_mul_64x32(key, static_cast<uint32_t>(sum)) : key * sum;
+  } else {
+    const uint64_t kj = lane_mul_64x32(key, *last);
+    r = lane_mul_64x32(kj, *last);
+#pragma unroll
+    for (int k = 1; k <= kW; ++k) {
+      if (kW == 1 || k <= width) {
+        const uint64_t t = lane_mul_64x32(kj, last[-k]);
+        r = t < r ? t : r;
+      }
+    }
+  }
+  return is_green(cbrng_lane(v, r), tm1);
+}
+
+constexpr int kStage = 4;   // tokens a lane loads at once when it stages a text
+template <int kSeeding, int kW, int kBlock>
+__global__ void __launch_bounds__(kBlock)
 detect_unique_kernel(const int32_t* __restrict__ tokens, int64_t N, int64_t L, int64_t row_stride,
                      int width, uint64_t key, uint32_t tm1, double gamma, uint32_t slots,
                      DetectIO io) {
-  extern __shared__ int32_t smem[];
-  int32_t* table = smem;           // `slots` entries, a power of two
-  int32_t* seq = smem + slots;     // the sequence's tokens (up to L)
+  extern __shared__ __attribute__((aligned(16))) int32_t smem[];
+  int32_t* table = smem;                                      // `slots` entries, a power of two >= 64
+  uint32_t* seq = reinterpret_cast<uint32_t*>(smem + slots);  // the staged sequence (up to L)
   __shared__ uint32_t sums[2];
   for (int64_t n = blockIdx.x; n < N; n += gridDim.x) {
     const int32_t* src = tokens + n * row_stride;
-    const int64_t len = sequence_length(io.lengths, n, L);
-    for (int64_t t = threadIdx.x; t < len; t += kUniqueBlock) seq[t] = src[t];
-    for (uint32_t sl = threadIdx.x; sl < slots; sl += kUniqueBlock) table[sl] = kEmptySlot;
-    if (kUniqueBlock > kWave && threadIdx.x < 2) sums[threadIdx.x] = 0u;
+    const int len = static_cast<int>(sequence_length(io.lengths, n, L));   // at most 4096 + kMaxWidth
+    for (int t0 = threadIdx.x; t0 < len; t0 += kStage * kBlock) {
+      uint32_t v[kStage];
+#pragma unroll
+      for (int u = 0; u < kStage; ++u) v[u] = static_cast<uint32_t>(src[min(t0 + u * kBlock, len - 1)]);
+#pragma unroll
+      for (int u = 0; u < kStage; ++u)
+        if (t0 + u * kBlock < len) seq[t0 + u * kBlock] = kSeeding == kSelfSalt ? jenkins32_lane(v[u]) : v[u];
+    }
+    typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
+    for (uint32_t sl = 4u * threadIdx.x; sl < slots; sl += 4u * kBlock)
+      *reinterpret_cast<i32x4*>(table + sl) = i32x4{kEmptySlot, kEmptySlot, kEmptySlot, kEmptySlot};
+    if (threadIdx.x < 2) sums[threadIdx.x] = 0u;
     __syncthreads();
-    uint32_t trials = 0u, green = 0u;
-    for (int64_t i = width + threadIdx.x; i < len; i += kUniqueBlock) {
-      const uint32_t h = ngram_hash(seq, i, width);
-      const uint32_t fp = h >> kSlotPosBits;
-      const int32_t mine = static_cast<int32_t>((fp << kSlotPosBits) | static_cast<uint32_t>(i));
+    uint32_t trials = 0u, green = 0u;   // of the wave (the same in every lane)
+    // a wave's first position decides whether it takes the pass: all its lanes go along
+    for (int base = width + static_cast<int>(threadIdx.x & ~63u); base < len; base += kBlock) {
+      const int i = min(base + static_cast<int>(threadIdx.x % 64u), len - 1);
+      const uint32_t* last = seq + i;
+      const uint32_t v = kSeeding == kSelfSalt ? static_cast<uint32_t>(src[i]) : *last;   // arrives while the lane probes
+      const uint32_t h = ngram_hash(last, width);
+      constexpr uint32_t kPos = (1u << kSlotPosBits) - 1u;
+      const uint32_t mine = (h & ~kPos) | static_cast<uint32_t>(i);
       uint32_t slot = h & (slots - 1u);
-      bool claimed = false;
+      bool looking = base + static_cast<int>(threadIdx.x % 64u) < len, claimed = false;
       // at most `slots` probes; the set never fills, so a lane stops long before
       for (uint32_t probe = 0; probe < slots; ++probe) {
-        const int32_t held = atomicCAS(&table[slot], kEmptySlot, mine);
-        if (held == kEmptySlot) { claimed = true; break; }
-        if ((static_cast<uint32_t>(held) >> kSlotPosBits) == fp &&
-            same_ngram(seq, static_cast<int64_t>(static_cast<uint32_t>(held) & ((1u << kSlotPosBits) - 1u)), i, width))
-          break;
-        slot = (slot + 1u) & (slots - 1u);
+        if (looking) {
+          const uint32_t held = static_cast<uint32_t>(atomicCAS(&table[slot], kEmptySlot, static_cast<int32_t>(mine)));
+          claimed = held == static_cast<uint32_t>(kEmptySlot);
+          looking = !claimed && !((held & ~kPos) == (mine & ~kPos) && same_ngram(seq + (held & kPos), last, width));
+          slot = (slot + 1u) & (slots - 1u);
+        }
+        if (!__any(looking)) break;
       }
-      if (claimed) {
-        uint32_t w[kW];
-#pragma unroll
-        for (int k = 0; k < kW; ++k)
-          w[k] = (kW == 1 || k < width) ? static_cast<uint32_t>(seq[i - width + k]) : 0u;
-        ++trials;
-        green += window_green<kSeeding, kW>(key, w, width, static_cast<uint32_t>(seq[i]), tm1)
-                     ? 1u : 0u;
-      }
+      trials += static_cast<uint32_t>(__popcll(__ballot(claimed)));
+      bool g = false;
+      if (claimed) g = staged_green<kSeeding, kW>(key, last, width, v, tm1);
+      green += static_cast<uint32_t>(__popcll(__ballot(g)));
     }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-      trials += __shfl_xor(trials, off, 64);
-      green += __shfl_xor(green, off, 64);
+    if (threadIdx.x % 64 == 0) {
+      atomicAdd(&sums[0], trials);
+      atomicAdd(&sums[1], green);
     }
-    if constexpr (kUniqueBlock == kWave) {
-      if (threadIdx.x == 0) detect_store(io, n, green, trials, gamma);
-    } else {
-      if (threadIdx.x % 64 == 0) {
-        atomicAdd(&sums[0], trials);
-        atomicAdd(&sums[1], green);
-      }
-      __syncthreads();
-      if (threadIdx.x == 0) detect_store(io, n, sums[1], sums[0], gamma);
-    }
-    __syncthreads();  // the table (and sums) are reset for the next sequence
+    __syncthreads();
+    if (threadIdx.x == 0) detect_store(io, n, sums[1], sums[0], gamma);
+    __syncthreads();  // the table and sums are reset for the next sequence
   }
 }
 
@@ -2078,14 +2108,39 @@ void launch_detect(int64_t positions, hipStream_t st, const int32_t* tokens, int
   else launch(std::integral_constant<int, 2>{});
 }
 
+// Threads of the workgroup that takes a text with the repeat rule: the most that its
+// positions keep busy while the launch stays within 4096 waves, as every text costs its waves'
+// launch, staging and barriers (about 1.6 waves start per ns); but enough for 24 waves a CU
+// where the texts' LDS lets only few workgroups share one.  us at 64 / 128 / 256 / 512 threads
+// (1024 for the last three): 4000 texts of 60 tokens 6.0 / 7.5 / 10.3 / 19.1; 4096 x 512 20.5 /
+// 15.2 / 16.1 / 21.3; 8000 x 1000 75 / 49 / 38 / 52; 1024 x 1024 25.1 / 15.3 / 11.0 / 11.7;
+// 512 x 512 11.4 / 7.4 / 5.7 / 5.1; 512 x 4096 140 / 81 / 45 / 31.7 (36); 256 x 1024 24.0 / 14.0 /
+// 9.0 / 6.9 (6.3); 16 x 4096 96 / 52 / 29.5 / 18.8 (14.0).  Before: 256 for every text, 29.6 us
+// for 16 x 4096.
+int unique_block(int64_t N, int64_t positions, size_t lds) {
+  int block = 64;
+  while (block < 1024 && block < positions &&
+         (N * 2 * block <= 64 * 4096 || static_cast<size_t>(block) * 160 * 1024 < 64 * 24 * lds))
+    block *= 2;
+  return block;
+}
+
 template <int kSeeding, int kW>
 void launch_detect_unique(int64_t N, hipStream_t st, const int32_t* tokens, int64_t L,
                           int64_t row_stride, int width, uint64_t key, uint32_t tm1, double gamma,
                           uint32_t slots, const DetectIO& io) {
   const size_t lds = (static_cast<size_t>(slots) + static_cast<size_t>(L)) * sizeof(int32_t);
-  hipLaunchKernelGGL((detect_unique_kernel<kSeeding, kW>), dim3(static_cast<uint32_t>(grid_for(N))),
-                     dim3(kUniqueBlock), lds, st, tokens, N, L, row_stride, width, key, tm1, gamma,
-                     slots, io);
+  auto launch = [&](auto block) {
+    constexpr int kBlock = decltype(block)::value;
+    hipLaunchKernelGGL((detect_unique_kernel<kSeeding, kW, kBlock>), dim3(static_cast<uint32_t>(grid_for(N))),
+                       dim3(kBlock), lds, st, tokens, N, L, row_stride, width, key, tm1, gamma, slots, io);
+  };
+  const int block = unique_block(N, L - width, lds);
+  if (block == 64) launch(std::integral_constant<int, 64>{});
+  else if (block == 128) launch(std::integral_constant<int, 128>{});
+  else if (block == 256) launch(std::integral_constant<int, 256>{});
+  else if (block == 512) launch(std::integral_constant<int, 512>{});
+  else launch(std::integral_constant<int, 1024>{});
 }
 
 // Every detect entry point: validation, then one launch.

@@ -116,3 +116,18 @@ def test_detect_ex_c5_full_size(env, seeding, ignore):
     assert_ex_equal(got, expect, f"c5 {seeding} {ignore}")
     # the watermarked half is still detected with shorter texts
     assert np.nanmin(got[2][c["N"] // 2:]) > 4.0
+
+
+@pytest.mark.parametrize("seeding,width", [("context", 1), ("self_salt", 1), ("self_salt", 4), ("context", 8)])
+@pytest.mark.parametrize("N,L", [(4200, 60), (2050, 72), (4100, 400), (1030, 270), (513, 530), (257, 1040),
+                                 (3, 1032), (2, 2100)])
+def test_repeat_rule_with_every_workgroup_size(env, seeding, width, N, L):
+    """64 to 1024 threads a text, by the number of texts, their length and its LDS; lengths
+    either side of the workgroup's threads."""
+    rng = np.random.default_rng(N + L + width)
+    tok = texts(rng, N, L, 300)
+    lengths = rng.integers(max(0, L - 70), L + 1, N).astype(np.int32)
+    lengths[:2] = (0, width)
+    say(f"repeat rule {seeding} h={width} N={N} L={L}")
+    got = run_detect_ex(env, tok, width, WIDE, 0.25, seeding, lengths, True, pad=1)
+    assert_ex_equal(got, oracle.detect_ex(tok, width, WIDE, 0.25, seeding, lengths=lengths, ignore_repeated=True))
