@@ -706,21 +706,21 @@ watermark_ss_slab_kernel(T* __restrict__ logits, int64_t row_stride, uint32_t V,
 // orders the values (every NaN above +inf, -0 equal to +0), the low word is
 // ~index, so the maximum key is the largest value at its smallest index.
 // ---------------------------------------------------------------------------
-// 16-byte vectors per lane in a sub-batch of the fused decoding pass, and sub-batches per
-// workgroup segment.  A longer segment gives each wave a larger sample for its bounds, but
-// every lane holds a sub-batch in registers.  Sampling fp32, 256 x 152064: 4 / 6 / 8 / 12
-// vectors 38.0 (two sub-batches) / 37.7 / 38.2 / 40.7 us; sampling bf16, 160 x 152064: 4 /
-// 5 / 6 / 8 vectors 26.0 / 25.4 / 25.5 / 27.9 us; greedy fp32, 256 x 152064: 28.0 us from 4
-// to 8.  Greedy bf16 takes two sub-batches, the second's loads in flight while the first
-// is scored: 900 x 152064, 4 x 1 / 2 x 2 / 3 x 2 / 3 x 4: 52.5 / 50.2 / 47.2 / 48.1 us.
+// 16-byte vectors per lane in a workgroup segment of the fused decoding pass, and the
+// sub-batches that a segment is taken in.  A longer segment gives each wave a larger sample
+// for its bounds, but every lane holds a sub-batch in registers.  Sampling fp32, 256 x
+// 152064: 4 / 6 / 8 / 12 vectors 44.4 / 37.7 / 38.2 / 40.7 us; sampling bf16, 160 x 152064:
+// 4 / 5 / 6 / 8 vectors 26.0 / 25.4 / 25.5 / 27.9 us; greedy fp32, 256 x 152064: 28.0 us from
+// 4 to 8.  Greedy bf16 takes two sub-batches, the second's loads in flight while the first
+// is scored.
 #ifndef SBW_DECODE_VECS_F32_GREEDY
 #define SBW_DECODE_VECS_F32_GREEDY 6
 #endif
 #ifndef SBW_DECODE_VECS_F32
-#define SBW_DECODE_VECS_F32 6          // sampling
+#define SBW_DECODE_VECS_F32 8          // sampling
 #endif
 #ifndef SBW_DECODE_VECS_BF16
-#define SBW_DECODE_VECS_BF16 3         // greedy
+#define SBW_DECODE_VECS_BF16 4         // greedy
 #endif
 #ifndef SBW_DECODE_VECS_BF16_SAMPLE
 #define SBW_DECODE_VECS_BF16_SAMPLE 5
@@ -1963,7 +1963,8 @@ constexpr int64_t kSmallDecodeGrid = 900;
 // The workspace is sized for segments of kArgmaxSegElems; none may be shorter.
 static_assert(vec_segment_elems<float>(SBW_DECODE_VECS_F32 / 2) >= kArgmaxSegElems &&
                   vec_segment_elems<float>(SBW_DECODE_VECS_F32_GREEDY / 2) >= kArgmaxSegElems &&
-                  vec_segment_elems<uint16_t>(SBW_DECODE_VECS_BF16 / 2) * SBW_DECODE_SUBS_BF16 >= kArgmaxSegElems &&
+                  vec_segment_elems<uint16_t>(SBW_DECODE_VECS_BF16 / 2) >= kArgmaxSegElems &&
+                  SBW_DECODE_VECS_BF16 % (2 * SBW_DECODE_SUBS_BF16) == 0 &&
                   vec_segment_elems<uint16_t>(SBW_DECODE_VECS_BF16_SAMPLE / 2) >= kArgmaxSegElems,
               "the segments of a row must fit its part of the workspace");
 
@@ -1980,9 +1981,9 @@ void launch_argmax(const void* logits, int64_t B, uint32_t V, int64_t row_stride
                    uint64_t* partials, hipStream_t stream) {
   const T* p = static_cast<const T*>(logits);
   const uint32_t rows = static_cast<uint32_t>(B < kMaxGridY ? B : kMaxGridY);
-  constexpr int kN = decode_vecs_for<T>(kSample);
-  constexpr int kNs = kN / 2;
   constexpr int kSub = decode_subs_for<T>(kSample);
+  constexpr int kN = decode_vecs_for<T>(kSample) / kSub;
+  constexpr int kNs = kN / 2;
   const bool crowded = sizeof(T) == 4 && !kSample &&
                        B * static_cast<int64_t>(V) * 4 >= SBW_XCD_ROWS_MIN_BYTES;
   const uint32_t spare_lds = crowded ? kCrowdedLds : 0u;
