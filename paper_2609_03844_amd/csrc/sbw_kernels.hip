@@ -712,7 +712,7 @@ watermark_ss_slab_kernel(T* __restrict__ logits, int64_t row_stride, uint32_t V,
 // 152064: 4 / 6 / 8 / 12 vectors 44.4 / 37.7 / 38.2 / 40.7 us; sampling bf16, 160 x 152064:
 // 4 / 5 / 6 / 8 vectors 26.0 / 25.4 / 25.5 / 27.9 us; greedy fp32, 256 x 152064: 28.0 us from
 // 4 to 8.  Greedy bf16 takes two sub-batches, the second's loads in flight while the first
-// is scored.
+// is scored: 900 x 152064, one / two 52.2 / 50.3 us (60.3 before).
 #ifndef SBW_DECODE_VECS_F32_GREEDY
 #define SBW_DECODE_VECS_F32_GREEDY 6
 #endif
@@ -1067,9 +1067,9 @@ __device__ __forceinline__ void score_queue(LaneBest& b, const uint32_t* q_v, co
 // 10 a token to bound it.  Testing vectors before tokens, the noise bound from the float's
 // bits (4 instructions, a gap of 0.17 instead of 0.84 between its bounds, so fewer tokens
 // queue) and the queue's count and the round keys in scalar registers took 256 x 152064
-// fp32 from 42.9 to 38 us (1100 -> 870 VALU instructions a wave), bf16 160 x 152064 from
+// fp32 from 42.9 to 38.5 us (1100 -> 870 VALU instructions a wave), bf16 160 x 152064 from
 // 28.9 to 25.3.  Greedy reads at the memory's rate in large launches (bf16 900 x 152064:
-// 60.8 -> 47.4 us, 5.8 TB/s).  Rows off 16 bytes took an element-wise kernel before that
+// 60.3 -> 50.3 us, 5.4 TB/s).  Rows off 16 bytes took an element-wise kernel before that
 // drew every token's colour: 48 x 128259, greedy bf16 self-salt width 4 / sampled fp32
 // context, 27.5 -> 7.9 us, 31.3 -> 12.8 us.
 template <typename T, int kSeeding, int kN, int kSub, int kW, bool kSample>
