@@ -28,6 +28,7 @@
 // context[b*width .. b*width+width-1] (the tokens before the step); position i of a
 // detected sequence sees tokens i-width .. i-1.  Width 1 is the previous token.
 #include <hip/hip_runtime.h>
+#include <float.h>
 #include <math.h>
 #include <stdint.h>
 
@@ -857,15 +858,23 @@ __device__ __forceinline__ float reach_bound(float m, float delta, uint16_t) {
   return fminf(m, widen(bias_bf16(static_cast<uint16_t>(b), delta, true)));
 }
 
-// A logit below which neither candidate value reaches lb: x + dplus, rounded (to 24 or 8
-// significant bits), is at most x + dplus + rel * (|lb| + dplus) where it reaches lb.
-// Bounds too large for the sums here keep every token.
+// A logit below which neither candidate value reaches lb (never a NaN): x + dplus, rounded
+// (to 24 or 8 significant bits), is at most x + dplus + rel * (|lb| + dplus) where it reaches
+// lb.  A bound of +inf is taken as the largest finite float, which a token that reaches it
+// reaches too; sums that overflow here give -inf, which keeps every token.
 __device__ __forceinline__ float reach_threshold(float lb, float dplus, float) {
-  return fabsf(lb) < 1e37f && dplus < 1e37f ? (lb - dplus) - 0x1p-21f * (fabsf(lb) + dplus) : -INFINITY;
+  const float c = fminf(lb, FLT_MAX);
+  return (c - dplus) - (0x1p-21f * fabsf(c) + 0x1p-21f * dplus);
 }
 __device__ __forceinline__ float reach_threshold(float lb, float dplus, uint16_t) {
-  return fabsf(lb) < 1e37f && dplus < 1e37f ? (lb - dplus) - 0x1p-7f * (fabsf(lb) + dplus) - 0x1p-130f
-                                            : -INFINITY;
+  const float c = fminf(lb, FLT_MAX);
+  return (c - dplus) - (0x1p-7f * fabsf(c) + 0x1p-7f * dplus) - 0x1p-130f;
+}
+// Sampling: what a token's bound without kNoiseBitsOffset has to reach for a score of at
+// least lb (the roundings of the bound are far below the relative term).
+__device__ __forceinline__ float reach_noise_threshold(float lb) {
+  const float c = fminf(lb, FLT_MAX);
+  return (c - kNoiseBitsOffset) - 0x1p-20f * (fabsf(c) + 256.0f);
 }
 
 // What a pass maximises: the watermarked logit (greedy decoding), or, for sampling,
@@ -1056,8 +1065,8 @@ __device__ __forceinline__ void score_queue(LaneBest& b, const uint32_t* q_v, co
 //     the wave's largest lower bound;
 //  2. a vector whose largest bound reaches lb in some lane has its tokens tested one by
 //     one, and those that reach lb join the wave's queue in LDS; a queue that would
-//     overflow is scored exactly, one token per lane, and at the end the four waves'
-//     queues are scored together.
+//     overflow is scored exactly, one token per lane, and lb rises to the best of these
+//     scores; at the end the four waves' queues are scored together.
 // lb only rises.  A token left out scores below lb, which some token of the wave's
 // share attains, so the partial equals that of a full scan.  Lanes see tokens out of index
 // order, so their running argmax breaks ties by index.  Rows start anywhere, as in the
@@ -1072,6 +1081,11 @@ __device__ __forceinline__ void score_queue(LaneBest& b, const uint32_t* q_v, co
 // 60.3 -> 50.3 us, 5.4 TB/s).  Rows off 16 bytes took an element-wise kernel before that
 // drew every token's colour: 48 x 128259, greedy bf16 self-salt width 4 / sampled fp32
 // context, 27.5 -> 7.9 us, 31.3 -> 12.8 us.
+//
+// A delta that is large against the logits' spread puts most tokens within reach of step
+// 1's bound; the exact scores then raise it past all but the green ones near the top
+// (64 x 128256 N(0,2), delta 8, with that rise / without: greedy fp32 13.7 / 32.3 us, bf16
+// 14.1 / 29.5; sampling fp32 19.6 / 48.2, bf16 31.3 / 45.7).
 template <typename T, int kSeeding, int kN, int kSub, int kW, bool kSample>
 __global__ void __launch_bounds__(kThreads)
 decode_vec_kernel(const T* __restrict__ logits, int64_t row_stride, uint32_t V, int64_t B,
@@ -1195,8 +1209,7 @@ decode_vec_kernel(const T* __restrict__ logits, int64_t row_stride, uint32_t V, 
         const bool upper_range = up - pm > kNoiseUpperRange + 0x1p-18f * (fabsf(pm) + 18.0f);
         const float lb_lane = up < INFINITY && upper_range ? up - slack : -INFINITY;
         lb = fmaxf(lb0, wave_max(lb_lane));
-        // a score of at least lb needs a bound of at least this (the roundings of hi)
-        reach = (lb - kNoiseBitsOffset) - 0x1p-20f * (fabsf(lb) + 256.0f);
+        reach = reach_noise_threshold(lb);
       }
 
       // Queue the tokens whose upper bound reaches lb.  The counters are the same in
@@ -1204,13 +1217,16 @@ decode_vec_kernel(const T* __restrict__ logits, int64_t row_stride, uint32_t V, 
 #pragma unroll
       for (int n = 0; n < kN; ++n) {
         const uint32_t j = sub_first + n * kThreads + threadIdx.x;
-        uint64_t lanes = __ballot(!(vm[n] < reach));
-        if (!whole) lanes &= __ballot(j < full);
-        if (lanes == 0u) continue;
         if (queued > 64u) {
           score_queue<T, kSeeding, kW, kSample>(best, q_v, q_raw, queued, rs, tm1, none_green, delta, sc);
           queued = 0;
+          // the exact scores raise the bound (a NaN among them leaves it)
+          lb = fmaxf(lb, wave_max(best.any ? best.v : -INFINITY));
+          reach = kSample ? reach_noise_threshold(lb) : reach_threshold(lb, dplus, T{});
         }
+        uint64_t lanes = __ballot(!(vm[n] < reach));
+        if (!whole) lanes &= __ballot(j < full);
+        if (lanes == 0u) continue;
         const uint32_t jid = id_first + n * kThreads + threadIdx.x;
 #pragma unroll
         for (int e = 0; e < kE; ++e) {
