@@ -1,7 +1,7 @@
 """GPU parity when rows (or row groups) outnumber the 65535 workgroups of a grid's y
 dimension, so every row-parallel kernel runs its grid-stride loop: many short rows
 for the watermark (both seedings; self-salt through the slab kernel with a window of
-one token and through the row-group kernel with a window of 4), greedy decoding,
+one token and through the row kernel with a window of 4), greedy decoding,
 sampling, candidates and both detection kernels."""
 import numpy as np
 import pytest
@@ -29,8 +29,8 @@ def test_watermark_many_rows(env, seeding, B, V):
 
 
 def test_watermark_window_many_rows(env):
-    """Self-salt with a window of 4 keeps one row per workgroup: 70001 aligned rows of
-    40 logits run the row-group kernel's grid-stride loop."""
+    """Self-salt with a window of 4: 70001 rows of 40 logits run the row kernel's
+    grid-stride loop."""
     torch, sbw, dev = env
     rng = np.random.default_rng(245)
     B, V = 70001, 40

@@ -157,9 +157,8 @@ def test_watermark_small(env, dtype, seeding, B, V):
 @pytest.mark.parametrize("stride_pad,offset", [(1, 0), (3, 0), (8, 0), (0, 1), (5, 3), (0, 8),
                                                (5, 0), (13, 8)])
 def test_watermark_layouts(env, dtype, seeding, stride_pad, offset):
-    # padded rows, unaligned row starts (element kernel) and aligned-but-offset starts;
-    # strides of 5008 and 5016 keep rows 16-byte aligned in both dtypes (the vector
-    # kernels with a 3-token row tail)
+    # padded rows, rows off 16 bytes and aligned-but-offset starts, all with a 3-token row
+    # tail; strides of 5008 and 5016 keep rows 16-byte aligned in both dtypes
     rng = np.random.default_rng(77 + stride_pad * 10 + offset)
     B, V = 6, 5003
     x = special_logits(rng, B, V, dtype)
@@ -343,7 +342,7 @@ def test_bf16_rounding_every_pattern(env, layout):
 def test_context_xcd_rows(env, dtype, B, V):
     """Context-seeded launches of at least 512 rows, a multiple of 8, and more logit
     bytes than the Infinity Cache holds renumber their workgroups so that each XCD takes
-    whole rows; rows padded to 16 bytes so that the vector kernel takes them."""
+    whole rows; the rows are padded to 16 bytes and their padding checked."""
     rng = np.random.default_rng(5120 + B + V)
     x = special_logits(rng, B, V, dtype)
     prev = rng.integers(0, 1 << 31, B).astype(np.int32)
@@ -362,20 +361,22 @@ def test_context_xcd_rows(env, dtype, B, V):
 
 
 @pytest.mark.parametrize("dtype,B,V,width,rows", [
-    ("f32", 75, 152063, 1, 4),      # 149 tiles x 19 / 20 groups of 4 rows, last group of 3 / 1;
-    ("f32", 77, 152061, 1, 4),      #   6-row slabs would make 13 x 149 < 2000 workgroups
-    ("bf16", 151, 152063, 1, 2),    # bf16 takes at most 2 rows; 4 groups per workgroup (the
-                                    #   next one loaded while the current one is drawn)
-    ("f32", 221, 151937, 4, 1),     # width 4 (SBW-ss-V) keeps one row per workgroup
-    ("f32", 63, 128256, 1, 4),      # c3's launch, last group of 3
-    ("f32", 33, 128256, 1, 4),      # last group of 1
-    ("bf16", 67, 128256, 1, 2),     # 2-row groups, two per workgroup, last group of 1
+    ("f32", 75, 152063, 1, 6),      # 75 tiles of 512 quads: 13 slots of 5 and 6 rows (6-row
+    ("f32", 77, 152061, 1, 6),      #   slabs would make 13 x 149 < 2000 workgroups)
+    ("bf16", 151, 152063, 1, 3),    # 51 slots of 2 and 3 rows
+    ("f32", 221, 151937, 4, 6),     # width 4 (SBW-ss-V), 37 slots of 5 and 6 rows
+    ("f32", 63, 128256, 1, 4),      # c3's launch, 16 slots of 3 and 4 rows
+    ("f32", 33, 128256, 1, 2),      # 17 slots of 1 and 2 rows
+    ("bf16", 67, 128256, 1, 3),     # 23 slots of 2 and 3 rows
 ])
 def test_self_salt_row_groups(env, dtype, B, V, width, rows):
-    """Self-salt launches of the sizes at which a workgroup shares the candidate terms
-    across `rows` rows (width 1 with enough workgroups), with a partial last vector
-    (rows padded to a multiple of 16 bytes, so that the vector kernels take them) and a
-    partial last row group."""
+    """Self-salt launches of the sizes at which a workgroup takes up to `rows` rows in turn
+    with its candidate terms computed once (slots of rows y, y + slots, ...), with a partial
+    last quad, and rows padded to a multiple of 16 bytes."""
+    tiles = -(-(V // 4) // 512)
+    costs = [(-(-tiles * -(-B // n) // 256) * (3 * n + 1), n) for n in range(1, 9)
+             if n == 1 or tiles * -(-B // n) >= 960]
+    assert min(costs)[1] == rows
     rng = np.random.default_rng(230 + B + width)
     x = special_logits(rng, B, V, dtype)
     ctx = workloads.context_tokens(B, width, V, rng)

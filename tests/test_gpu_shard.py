@@ -7,8 +7,8 @@ A shard holds columns [a, b) of the vocabulary; column c is token a + c.  Checke
     best of its slice assembled from the oracle's watermark and noise;
   * the shards' winners, reduced as a tensor-parallel head would (largest value,
     smallest id among equal ones, NaN above all), equal the oracle's full-row decode;
-  * shards whose first id is or is not a multiple of 4 (fp32) / 8 (bf16), so both the
-    vector and the element kernels run, and ids up to 2^31 - 1;
+  * shards whose first id is or is not a multiple of 4 (fp32) / 8 (bf16), so rows with and
+    without single columns before their first vector run, and ids up to 2^31 - 1;
   * the 8-way split of the 152064-token vocabulary at B = 256, as views of one tensor;
   * detection split along the text, each shard reading a halo of width tokens.
 """
@@ -23,8 +23,8 @@ from test_gpu_parity import WIDE, _from_device, _to_device, assert_logits_equal,
 pytestmark = pytest.mark.gpu
 
 # Boundaries of a 40001-token vocabulary: shard starts 0, 8192 and 20000 are multiples
-# of 8; 24004 is a multiple of 4 only (fp32 vector kernels, bf16 element kernels); 8195
-# and 27331 are odd; one shard is 3 tokens long.
+# of 8; 24004 is a multiple of 4 only (bf16 rows start inside a vector); 8195 and 27331
+# are odd; one shard is 3 tokens long.
 BOUNDS = [0, 8192, 8195, 20000, 24004, 27331, 40001]
 
 

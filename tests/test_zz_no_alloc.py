@@ -82,7 +82,7 @@ CASES = [
     # (B, V, dtype, width, seeding, gamma, delta, pad, offset): each later case is smaller
     (256, 152064, "f32", 1, "self_salt", 0.25, 2.0, 0, 0),
     (37, 32001, "bf16", 4, "context", 0.5, 4.0, 0, 0),
-    (5, 6000, "f32", 1, "context", 0.25, -3.0, 3, 1),      # unaligned rows: element path
+    (5, 6000, "f32", 1, "context", 0.25, -3.0, 3, 1),      # rows off 16 bytes
     (1, 7, "bf16", 2, "self_salt", 1.0, 2.0, 0, 0),
 ]
 
