@@ -49,7 +49,10 @@
  *   - Work is enqueued on `stream` (a hipStream_t; NULL = the null stream) and the
  *     call returns without synchronising the host.  Functions hold no global
  *     mutable state and are reentrant, except sbw_watermark_argmax_noalloc, whose
- *     scratch array is shared by all of its calls on a device.
+ *     scratch array is shared by all of its calls on a device.  Calls that overlap in
+ *     time may share inputs but no output or workspace: an output may be written more
+ *     than once on the way (detect keeps partial counts in z), so even equal calls on
+ *     one output must be ordered, for instance by one stream.
  *   - All arguments are checked on the host before any HIP call, so an error
  *     return means nothing was enqueued.  Token values are not checked (that
  *     would need a device read): every definition holds for any 32-bit pattern.
@@ -115,8 +118,8 @@ typedef enum SBW_ENUM_TYPE {
  *   seeding      SBW_SEED_CONTEXT or SBW_SEED_SELF_SALT.
  *   stream       hipStream_t to enqueue on.
  *
- * Rows whose start is 16-byte aligned take 128-bit loads and stores; other
- * layouts are correct but slower.
+ * Rows may start at any element; those whose starts are 16-byte aligned are faster by up to
+ * a tenth.
  */
 sbw_status_t sbw_watermark(void *logits, sbw_dtype_t dtype, int64_t B, int64_t V,
                            int64_t row_stride, const int32_t *prev_tokens, uint64_t key,
@@ -150,8 +153,13 @@ sbw_status_t sbw_green_mask(uint32_t *bits, int64_t B, int64_t V, const int32_t 
  *                SBW_ERR_GAMMA.
  *   green_counts device, [N] int32, written: W per sequence.
  *   z            device, [N] double, written: (W - T*gamma) / sqrt(T*gamma*(1-gamma)),
- *                evaluated in binary64 in that order.
+ *                evaluated in binary64 in that order.  Also the call's scratch for long
+ *                sequences (zeroed, then 64-bit atomic adds): its contents on entry do not
+ *                matter, and it may be device, managed (hipMallocManaged) or pinned host
+ *                memory (hipHostMalloc), on which the device's integer atomics work.
  *   L is limited to 2^31 - 1 (SBW_ERR_UNSUPPORTED beyond).
+ * Enqueues one kernel on `stream`, or two (the first clears z) where several workgroups
+ * share a long sequence; no memset, so the call can be captured in a HIP graph.
  */
 sbw_status_t sbw_detect(const int32_t *tokens, int64_t N, int64_t L, int64_t row_stride,
                         uint64_t key, double gamma, sbw_seeding_t seeding,
@@ -214,9 +222,11 @@ typedef enum SBW_ENUM_TYPE {
  *                SBW_ERR_UNSUPPORTED.
  *   green_counts device, [N] int32, written.
  *   scored       device, [N] int32 or NULL: T of each sequence, written.
- *   z            device, [N] double, written; NaN when T == 0.
- * One kernel on `stream`: one wavefront per sequence, or, with the repeat rule, one
- * workgroup per sequence with an LDS hash set (no global memory is allocated).
+ *   z            device, [N] double, written; NaN when T == 0.  Scratch as for sbw_detect.
+ * One kernel on `stream`, or two for long sequences, as for sbw_detect: a sequence is
+ * shared by one wavefront, the wavefronts of a workgroup or several workgroups, by the
+ * number of sequences and their length.  With the repeat rule one kernel, one workgroup per
+ * sequence with an LDS hash set (no global memory is allocated).
  */
 sbw_status_t sbw_detect_ex(const int32_t *tokens, int64_t N, int64_t L, int64_t row_stride,
                            const int32_t *lengths, int64_t width, uint64_t key, double gamma,
@@ -356,7 +366,7 @@ sbw_status_t sbw_watermark_argmax_noalloc(const void *logits, sbw_dtype_t dtype,
  * is the shards' winner with the largest value (or score), the smallest global id
  * among equal ones, a NaN above everything: the reduction the unsharded call makes
  * over its own segments.  Rows whose first id is not a multiple of 4 (fp32) or 8
- * (bf16) take the element-wise kernels, which give the same results.
+ * (bf16) have a few columns before their first 128-bit vector, which are taken one by one.
  */
 sbw_status_t sbw_watermark_shard(void *logits, sbw_dtype_t dtype, int64_t B, int64_t V,
                                  int64_t row_stride, const int32_t *context, int64_t width,

@@ -506,7 +506,8 @@ def detect(tokens: torch.Tensor, key: int, gamma: float, seeding="context",
            counts: torch.Tensor | None = None, z: torch.Tensor | None = None, stream=None,
            width: int = 1):
     """Green count and z-score per sequence of tokens [N, L] int32 (unit stride along L).
-    Positions width..L-1 are scored under the `width` tokens before each (T = L - width)."""
+    Positions width..L-1 are scored under the `width` tokens before each (T = L - width).
+    z holds partial counts on the way: calls that overlap in time must not share outputs."""
     if stream is None:
         out = _native.detect(tokens, key, gamma, seeding, width, None, False, counts, False, z)
         if out is not None:
