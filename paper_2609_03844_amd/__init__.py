@@ -509,7 +509,7 @@ def detect(tokens: torch.Tensor, key: int, gamma: float, seeding="context",
     Positions width..L-1 are scored under the `width` tokens before each (T = L - width).
     z holds partial counts on the way: calls that overlap in time must not share outputs."""
     if stream is None:
-        out = _native.detect(tokens, key, gamma, seeding, width, None, False, counts, False, z)
+        out = _native.detect(tokens, key, gamma, seeding, width, None, False, counts, z)
         if out is not None:
             return out if type(out) is tuple else _check(out)
     if tokens.dtype != torch.int32 or tokens.dim() != 2:
@@ -543,8 +543,8 @@ def detect_ex(tokens: torch.Tensor, key: int, gamma: float, seeding="context", w
     (width+1)-gram of a text is scored once (L - width <= 4096).  Returns (green
     counts int32 [N], scored positions int32 [N], z float64 [N])."""
     if stream is None:
-        out = _native.detect(tokens, key, gamma, seeding, width, lengths, ignore_repeated, counts,
-                             scored, z)
+        out = _native.detect(tokens, key, gamma, seeding, width, lengths, ignore_repeated, counts, z,
+                             scored)
         if out is not None:
             return out if type(out) is tuple else _check(out)
     if tokens.dtype != torch.int32 or tokens.dim() != 2:

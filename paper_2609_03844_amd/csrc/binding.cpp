@@ -279,12 +279,12 @@ PyObject* decode(PyObject*, PyObject* const* a, Py_ssize_t n) {
   });
 }
 
-// detect(tokens, key, gamma, seeding, width, lengths, ignore_repeated, counts, scored, z):
-// scored False leaves the scored positions out (two outputs)
+// detect(tokens, key, gamma, seeding, width, lengths, ignore_repeated, counts, z[, scored]):
+// without `scored` the scored positions are left out (two outputs)
 PyObject* detect(PyObject*, PyObject* const* a, Py_ssize_t n) {
   return guarded([&]() -> PyObject* {
     Call c;
-    if (n != 10 || !matrix_of(a[0], &c) || c.matrix->scalar_type() != at::kInt || !key_of(a[1], &c.key) ||
+    if (n < 9 || n > 10 || !matrix_of(a[0], &c) || c.matrix->scalar_type() != at::kInt || !key_of(a[1], &c.key) ||
         !number(a[2], &c.gamma) || !seeding_of(a[3], &c.seeding) || !integer(a[4], &c.width) ||
         !PyBool_Check(a[6]))
       Py_RETURN_NONE;
@@ -293,11 +293,11 @@ PyObject* detect(PyObject*, PyObject* const* a, Py_ssize_t n) {
       lengths = packed_of(a[5], at::kInt, c.device);
       if (lengths == nullptr || lengths->dim() != 1 || lengths->size(0) != c.rows) Py_RETURN_NONE;
     }
-    const bool with_scored = a[8] != Py_False;
+    const bool with_scored = n == 10;
     Tensor counts, scored, z;
     if (!output_of(a[7], c.rows, at::kInt, c, &counts) ||
-        (with_scored && !output_of(a[8], c.rows, at::kInt, c, &scored)) ||
-        !output_of(a[9], c.rows, at::kDouble, c, &z))
+        (with_scored && !output_of(a[9], c.rows, at::kInt, c, &scored)) ||
+        !output_of(a[8], c.rows, at::kDouble, c, &z))
       Py_RETURN_NONE;
     const auto* tokens = static_cast<const int32_t*>(c.matrix->data_ptr());
     const auto* length = lengths != nullptr ? static_cast<const int32_t*>(lengths->data_ptr()) : nullptr;
@@ -307,8 +307,8 @@ PyObject* detect(PyObject*, PyObject* const* a, Py_ssize_t n) {
     const uint32_t flags = a[6] == Py_True ? SBW_DETECT_IGNORE_REPEATED : 0u;
     void* stream = stream_of(c);
     PyObject* first = object_of(a[7], counts);
-    PyObject* last = object_of(a[9], z);
-    PyObject* outputs = with_scored ? tuple_of(first, object_of(a[8], scored), last)
+    PyObject* last = object_of(a[8], z);
+    PyObject* outputs = with_scored ? tuple_of(first, object_of(a[9], scored), last)
                                     : tuple_of(first, last, nullptr);
     if (outputs == nullptr) return nullptr;
     return outputs_or_status(outputs, unlocked([&] {

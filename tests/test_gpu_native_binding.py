@@ -84,6 +84,9 @@ def test_refused_calls_and_other_forms(env):
         (lambda: sbw.detect(t, WIDE, 0.0), sbw.SbwError),
         (lambda: sbw.detect(t, WIDE, 0.25, width=9), sbw.SbwError),
         (lambda: sbw.detect(t[:, ::2], WIDE, 0.25), ValueError),
+        (lambda: sbw.detect_ex(t, WIDE, 0.25, scored=False), AttributeError),   # not a tensor
+        (lambda: sbw.detect_ex(t, WIDE, 0.25, counts=False), AttributeError),
+        (lambda: sbw.detect_ex(t, WIDE, 0.25, scored=p.long()), ValueError),
     ]
     for call, error in refused:
         with pytest.raises(error):
