@@ -75,10 +75,13 @@ class SbwError(RuntimeError):
         super().__init__(text)
 
 
+_BUILD_HINT = ("run __graft_entry__.build() or, as a file, "
+               f"python {os.path.join(os.path.dirname(os.path.abspath(__file__)), '_build.py')}")
+
+
 def _load() -> ctypes.CDLL:
     if not os.path.exists(LIBRARY):
-        raise ImportError(f"libsbw.so not built at {LIBRARY}; run __graft_entry__.build() "
-                          "or python -m paper_2609_03844_amd._build")
+        raise ImportError(f"libsbw.so not built at {LIBRARY}; {_BUILD_HINT}")
     lib = ctypes.CDLL(LIBRARY)
     P, i64, u64, f64, f32, i32 = (ctypes.c_void_p, ctypes.c_int64, ctypes.c_uint64,
                                   ctypes.c_double, ctypes.c_float, ctypes.c_int)
@@ -129,7 +132,11 @@ def _load() -> ctypes.CDLL:
 
 
 _lib = _load()
-from . import _binding as _native  # noqa: E402  (linked against libsbw.so)
+try:
+    from . import _binding as _native  # noqa: E402  (linked against libsbw.so)
+except ImportError as e:
+    raise ImportError(f"_binding.so next to {LIBRARY} is not built or does not load ({e}); "
+                      f"{_BUILD_HINT}") from e
 
 
 def library_path() -> str:

@@ -18,6 +18,7 @@ BINDING = os.path.join(PKG, "_binding.so")
 BINDING_SOURCE = os.path.join(CSRC, "binding.cpp")
 RATE_LIBRARY = os.path.join(PKG, "libsbw_rate.so")
 RATE_SOURCES = [os.path.join(CSRC, "philox_rate.hip")]
+ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 HEADERS = [os.path.join(CSRC, "sbw_device.hpp"), os.path.join(INCLUDE, "sbw.h")]
 
 HIPCC_FLAGS = [
@@ -39,7 +40,7 @@ HIPCC_FLAGS = [
 
 
 def hipcc() -> str:
-    for cand in (os.environ.get("HIPCC"), "/opt/rocm/bin/hipcc"):
+    for cand in (os.environ.get("HIPCC"), os.path.join(ROCM, "bin", "hipcc")):
         if cand and os.path.exists(cand):
             return cand
     return "hipcc"
@@ -67,7 +68,7 @@ def build_binding() -> str:
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
            "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", "-I", INCLUDE, "-isystem", include,
            "-isystem", os.path.join(include, "torch", "csrc", "api", "include"),
-           "-isystem", "/opt/rocm/include", "-isystem", sysconfig.get_paths()["include"],
+           "-isystem", os.path.join(ROCM, "include"), "-isystem", sysconfig.get_paths()["include"],
            BINDING_SOURCE, "-o", BINDING + ".tmp", "-L", PKG, "-lsbw", "-L", lib, "-ltorch_python",
            "-ltorch_cpu", "-lc10", "-lc10_hip", "-Wl,-rpath,$ORIGIN", "-Wl,-rpath," + lib]
     subprocess.run(cmd, check=True)
