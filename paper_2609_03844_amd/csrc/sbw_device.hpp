@@ -351,29 +351,18 @@ __device__ __forceinline__ float gumbel_of(uint32_t x) {
 constexpr float kGumbelLo = -3.0f;
 constexpr float kGumbelHi = 17.0f;
 
-// Bounds of gumbel_of from the leading one bits of the draw, for passes that skip
-// tokens whose noise cannot lift them to the best score.  With c the number of
-// leading ones of x, capped at 23, q = 1 - u = n 2^-24 for an odd n whose top bit
-// is bit 23 - c, so q lies in [2^-(c+1), 2^-c) (q = 2^-24 when c = 23).
-//  * Above: t = -log(1 - q) > q, so G = -log t < -log q <= (c + 1) ln 2.
-//  * Below, for c >= 2: G increases with u, so it exceeds its value at
-//    u = 1 - 2^-c, -log(-log(1 - 2^-c)) = c ln 2 - e(c) with e(2) = 0.1404 and e
-//    falling toward 0 as c grows; so G > (c + 1) ln 2 - (ln 2 + 0.1404).
-// Both hold, with room for the rounding of the fp32 logarithm, for every one of the 2^23
-// values of u.
-constexpr float kLn2f = 0.693147182f;                    // ln 2 rounded up
-constexpr float kGumbelMargin = 0.0009765625f;           // 2^-10
-constexpr float kGumbelGap = 0.8442f;                    // (c + 1) ln 2 + margin - G for c >= 2
-
-// The passes take a finer form of the same bounds.  y = 2^32 q = (~x & ~511) | 256 is exact
-// in fp32, and the bits of a float read as an integer are 2^23 (127 + e + f) for the value
-// 2^e (1 + f), with log2(1 + f) in [f, f + 0.0861).  So with b those bits of y (rounded to
-// 24 significant bits when converted), -log q lies in (159 - b / 2^23) ln 2 - [0, 0.0597),
-// where 159 = 127 + 32, and
-//  * G < kNoiseBitsOffset - kNoiseBitsScale * b, the offset with the margin in it;
+// Bounds of gumbel_of from the tail probability q = 1 - u of the draw, for passes that skip
+// tokens whose noise cannot lift them to the best score.  With t = -log(1 - q) > q, G = -log t
+// lies below -log q, by -log q - G = log(t / q), which grows with q and is 0.1404 at q = 1/4.
+// y = 2^32 q = (~x & ~511) | 256 is exact in fp32, and the bits of a float read as an integer
+// are 2^23 (127 + e + f) for the value 2^e (1 + f), with log2(1 + f) in [f, f + 0.0861).  So
+// with b those bits of y (rounded to 24 significant bits when converted), -log q lies in
+// (159 - b / 2^23) ln 2 - [0, 0.0597), where 159 = 127 + 32, and
+//  * G < kNoiseBitsOffset - kNoiseBitsScale * b, the offset with a margin of 2^-10 for the
+//    rounding of the fp32 logarithms;
 //  * for q < 1/4 (so for every draw whose bound exceeds kNoiseUpperRange), G is above that
-//    bound less kNoiseGap (e(2) + 0.0597 + the margin would do; the largest gap is 0.1647).
-// Checked for every one of the 2^23 values of u, like the coarse form.
+//    bound less kNoiseGap (0.1404 + 0.0597 + the margin would do; the largest gap is 0.1647).
+// Both hold for every one of the 2^23 values of u.
 constexpr float kNoiseBitsScale = 8.26295832e-08f;       // ln 2 / 2^23
 constexpr float kNoiseBitsOffset = 110.211402f;          // 159 ln 2 + 2^-10
 constexpr float kNoiseGap = 0.17f;

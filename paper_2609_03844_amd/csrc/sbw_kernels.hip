@@ -56,10 +56,7 @@ namespace {
 // costs more than the shorter slabs' extra self terms.  bf16: 12-row slabs from
 // SBW_SLAB_BF16_MIN_GROUPS, B = 1024 of 152064 (6450 workgroups: 215 us, row kernel 228);
 // below the row kernel is at least as fast (B = 512, 3225: 116.1 / 115.7; B = 256:
-// 62.5 / 59.1; B = 128 of 128256: 32.0 / 27.7).  SBW_SELF_SALT_SLAB 0 = off.
-#ifndef SBW_SELF_SALT_SLAB
-#define SBW_SELF_SALT_SLAB 1
-#endif
+// 62.5 / 59.1; B = 128 of 128256: 32.0 / 27.7).
 // Context seeding: launches of at least SBW_XCD_ROWS_MIN rows (a multiple of 8) and
 // SBW_XCD_ROWS_MIN_BYTES of logits, more than the 256 MB Infinity Cache holds, give
 // each XCD whole rows (fp32 B = 512 / 1024 of 152064: 1 / 3 % faster, bf16 B = 1024:
@@ -1399,31 +1396,19 @@ __device__ __forceinline__ uint64_t wave_shift_right(uint64_t x, uint64_t first)
   return (static_cast<uint64_t>(hi) << 32) | lo;
 }
 
-// Membership of token v at a position whose window is w[0..width-1].
-template <int kSeeding, int kW>
-__device__ __forceinline__ bool window_green(uint64_t key, const uint32_t (&w)[kW], int width,
-                                             uint32_t v, uint32_t tm1) {
+// Context seeding: membership of token v at a position whose window is w[0..width-1].
+template <int kW>
+__device__ __forceinline__ bool context_green(uint64_t key, const uint32_t (&w)[kW], int width,
+                                              uint32_t v, uint32_t tm1) {
   uint64_t r;
-  if (kSeeding == kContext) {
-    if constexpr (kW == 1) {
-      r = lane_mul_64x32(key, w[0]);
-    } else {
-      uint64_t sum = 0u;
-#pragma unroll
-      for (int i = 0; i < kW; ++i)
-        if (i < width) sum += w[i];
-      r = key * sum;
-    }
+  if constexpr (kW == 1) {
+    r = lane_mul_64x32(key, w[0]);
   } else {
-    const uint32_t jv = jenkins32_lane(v);
-    r = mul_64x64(key, wide_mul(jv, jv));
+    uint64_t sum = 0u;
 #pragma unroll
-    for (int i = 0; i < kW; ++i) {
-      if (kW == 1 || i < width) {
-        const uint64_t t = lane_mul_64x32(key * static_cast<uint64_t>(jenkins32_lane(w[i])), jv);
-        r = t < r ? t : r;
-      }
-    }
+    for (int i = 0; i < kW; ++i)
+      if (i < width) sum += w[i];
+    r = key * sum;
   }
   return is_green(cbrng_lane(v, r), tm1);
 }
@@ -1555,7 +1540,7 @@ __device__ __forceinline__ uint32_t detect_pass(const int32_t* seq, uint32_t bas
     }
   } else {
 #pragma unroll
-    for (int c = 0; c < kChunk; ++c) g[c] = window_green<kSeeding, kW>(key, w[c], width, v[c], tm1);
+    for (int c = 0; c < kChunk; ++c) g[c] = context_green<kW>(key, w[c], width, v[c], tm1);
   }
   // Chunks before rem / 64 lie inside the sequence, the next one holds its last rem % 64
   // positions, the others none (masks in scalar registers).
@@ -1680,7 +1665,10 @@ static_assert(kMaxUniqueSlots / 2 + kMaxWidth < (1u << kSlotPosBits) - 1u,
 // its steps is), so equal n-grams are those of equal J, and no position hashes its window
 // again.  `seq` below holds J(token) (self-salt) or the token (context).
 __device__ __forceinline__ uint32_t ngram_hash(const uint32_t* last, int width) {
-  // a sum of products with odd constants, then mixed downwards for the slot's low bits
+  // A sum of products with odd constants, then mixed downwards for the slot's low bits.  The
+  // multipliers are published ones: 2^32 over the golden ratio (Knuth), MurmurHash3's
+  // finaliser (A. Appleby), and a two-round xorshift-multiply hash of C. Wellons' search for
+  // integer hashes; any odd ones give the same results.
   uint32_t h = 0u, m = 0x9E3779B1u;
   for (int k = 0; k <= width; ++k) {
     h += last[-k] * m;
@@ -1864,7 +1852,7 @@ void launch_watermark(void* logits, int64_t B, uint32_t V, int64_t row_stride,
   const uint64_t vectors = sp.full;
   const uint32_t edge = sp.head + sp.tail != 0u ? 1u : 0u;   // a workgroup column for the edges
   if constexpr (kSeeding == kSelfSalt) {
-    if constexpr (SBW_SELF_SALT_SLAB && kW == 1) {
+    if constexpr (kW == 1) {
       const uint32_t tiles1 = static_cast<uint32_t>((vectors + kThreads - 1) / kThreads);
       auto launch_slab = [&](auto height) -> bool {
         constexpr int kRows = decltype(height)::value;
@@ -1922,8 +1910,8 @@ template <typename T>
 void dispatch_watermark(void* logits, int64_t B, uint32_t V, int64_t row_stride,
                         const int32_t* context, int width, uint64_t key, uint32_t tm1, float delta,
                         sbw_seeding_t seeding, uint32_t vbase, hipStream_t st) {
-  // Context seeding folds any window into one row seed; self-salt needs the window
-  // per candidate, so wider windows take the kMaxWidth instantiation.
+  // Context seeding folds any window into one row seed; self-salt needs the window per
+  // candidate and has an instantiation for each width.
   if (seeding == SBW_SEED_CONTEXT)
     launch_watermark<T, kContext, kMaxWidth>(logits, B, V, row_stride, context, width, key, tm1,
                                              delta, vbase, st);
