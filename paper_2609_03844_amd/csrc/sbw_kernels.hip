@@ -1968,13 +1968,15 @@ constexpr uint64_t vec_segment_elems(int kN) { return (16u / sizeof(T)) * kThrea
 // (twice the segments), which hides more of the load latency when the chip is not
 // full: a vocabulary shard of 19008 fp32 or bf16 logits at B = 256 gets 1280
 // workgroups instead of 768 (about 8 % faster); B = 64 rows of 152064 (960-1600
-// workgroups) stay.
+// workgroups) stay.  Such a launch takes them in one sub-batch: with few waves in flight a
+// second one only adds its bounds and test (greedy bf16, rows of 128256, two / one: B = 1
+// 5.37 / 5.26 us, B = 32 6.95 / 6.75, N(0,1) logits 9.27 / 8.80).
 constexpr int64_t kSmallDecodeGrid = 900;
 // The workspace is sized for segments of kArgmaxSegElems; none may be shorter.
 static_assert(vec_segment_elems<float>(SBW_DECODE_VECS_F32 / 2) >= kArgmaxSegElems &&
                   vec_segment_elems<float>(SBW_DECODE_VECS_F32_GREEDY / 2) >= kArgmaxSegElems &&
                   vec_segment_elems<uint16_t>(SBW_DECODE_VECS_BF16 / 2) >= kArgmaxSegElems &&
-                  SBW_DECODE_VECS_BF16 % (2 * SBW_DECODE_SUBS_BF16) == 0 &&
+                  SBW_DECODE_VECS_BF16 % SBW_DECODE_SUBS_BF16 == 0 &&
                   vec_segment_elems<uint16_t>(SBW_DECODE_VECS_BF16_SAMPLE / 2) >= kArgmaxSegElems,
               "the segments of a row must fit its part of the workspace");
 
@@ -1993,13 +1995,13 @@ void launch_argmax(const void* logits, int64_t B, uint32_t V, int64_t row_stride
   const uint32_t rows = static_cast<uint32_t>(B < kMaxGridY ? B : kMaxGridY);
   constexpr int kSub = decode_subs_for<T>(kSample);
   constexpr int kN = decode_vecs_for<T>(kSample) / kSub;
-  constexpr int kNs = kN / 2;
+  constexpr int kNs = kN * kSub / 2;
   const bool crowded = sizeof(T) == 4 && !kSample &&
                        B * static_cast<int64_t>(V) * 4 >= SBW_XCD_ROWS_MIN_BYTES;
   const uint32_t spare_lds = crowded ? kCrowdedLds : 0u;
-  auto launch = [&](auto vecs, uint64_t seg) {
+  auto launch = [&](auto vecs, auto subs, uint64_t seg) {
     const uint32_t segments = static_cast<uint32_t>((uint64_t{V} + seg - 1) / seg);
-    hipLaunchKernelGGL((decode_vec_kernel<T, kSeeding, decltype(vecs)::value, kSub, kW, kSample>),
+    hipLaunchKernelGGL((decode_vec_kernel<T, kSeeding, decltype(vecs)::value, decltype(subs)::value, kW, kSample>),
                        dim3(segments, rows), dim3(kThreads), spare_lds, stream, p, row_stride, V, B, context,
                        width, key, tm1, none, delta, sa.seeds, sa.inv_t, segments, partials, vbase);
     return segments;
@@ -2007,9 +2009,10 @@ void launch_argmax(const void* logits, int64_t B, uint32_t V, int64_t row_stride
   const uint64_t seg = vec_segment_elems<T>(kN) * kSub;
   uint32_t segments;
   if ((V + static_cast<int64_t>(seg) - 1) / static_cast<int64_t>(seg) * rows >= kSmallDecodeGrid)
-    segments = launch(std::integral_constant<int, kN>{}, seg);
+    segments = launch(std::integral_constant<int, kN>{}, std::integral_constant<int, kSub>{}, seg);
   else
-    segments = launch(std::integral_constant<int, kNs>{}, vec_segment_elems<T>(kNs) * kSub);
+    segments = launch(std::integral_constant<int, kNs>{}, std::integral_constant<int, 1>{},
+                      vec_segment_elems<T>(kNs));
   const int64_t row_blocks = grid_for((B + kThreads / 64 - 1) / (kThreads / 64));
   hipLaunchKernelGGL(argmax_finish_kernel, dim3(row_blocks), dim3(kThreads), 0, stream, partials,
                      segments, B, tokens, values);
