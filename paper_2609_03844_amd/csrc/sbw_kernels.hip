@@ -1431,15 +1431,19 @@ __device__ __forceinline__ int64_t sequence_length(const int32_t* lengths, int64
   return len < 0 ? 0 : (len > L ? L : len);
 }
 
+// `shared`: other workgroups have added into the z slot, so the store is atomic as their adds
+// are.  The others' is a plain one: written through at device scope it delayed the launch's end
+// (4 texts of 20 tokens, context: 2.51 us with it, 2.36 without).
 __device__ __forceinline__ void detect_store(const DetectIO& io, int64_t n, uint32_t green,
-                                             int64_t T, double gamma) {
+                                             int64_t T, double gamma, bool shared = false) {
   const double t = static_cast<double>(T);
   const double numerator = static_cast<double>(green) - t * gamma;
   const double denominator = sqrt(t * gamma * (1.0 - gamma));
   io.counts[n] = static_cast<int32_t>(green);
   if (io.scored != nullptr) io.scored[n] = static_cast<int32_t>(T);
-  // atomic, as detect_split_kernel's adds into the same slot are
-  __hip_atomic_store(&io.z[n], numerator / denominator, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const double z = numerator / denominator;
+  if (shared) __hip_atomic_store(&io.z[n], z, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  else io.z[n] = z;
 }
 
 // One wave's pass: the green positions among base .. base + 64 * kChunk - 1 of a sequence
@@ -1635,7 +1639,7 @@ detect_split_kernel(const int32_t* __restrict__ tokens, int64_t L, int64_t row_s
     if (static_cast<uint32_t>(before >> 32) != splits - 1u) return;
     sum += static_cast<uint32_t>(before);
   }
-  detect_store(io, n, sum, len > static_cast<uint32_t>(width) ? len - width : 0, gamma);
+  detect_store(io, n, sum, len > static_cast<uint32_t>(width) ? len - width : 0, gamma, splits > 1u);
 }
 
 // Zeroes the z slots that detect_split_kernel adds into.
@@ -2048,13 +2052,18 @@ void dispatch_argmax(const void* logits, int64_t B, uint32_t V, int64_t row_stri
 //  * A wave per sequence (detect_kernel) where the sequences alone fill the chip: above
 //    1024 of them with a window of one token (N = 2048, L = 512, context: 4.3 us against
 //    4.8 with 4 waves), above 2048 with wider windows (N = 2048, L = 512 / 1024, width 4:
-//    context 5.5 / 7.8 us with 4 waves against 7.0 / 11.2).  Chunks per pass: the most that
-//    pad a sequence by at most an eighth (N = 16384, L = 300, self-salt: 15.2 us with one
-//    chunk, 20.8 with 8; N = 4096, L = 512: 7.7 against 7.1 the other way).
-//  * Below, up to 16 waves share a sequence, as many as keep 8192 waves in all and one
-//    chunk each (two each from 512 sequences: N = 1024, L = 512, self-salt 4.1 us, one each
-//    4.4); two chunks a pass where a wave has them.  N = 128, L = 2048, self-salt width 4:
-//    19.6 -> 4.5 us.
+//    context 5.5 / 7.8 us with 4 waves against 7.0 / 11.2); and where a sequence has too few
+//    chunks for the sharing to pay: two from 256 sequences (N = 1000, L = 80, context 2.64 us,
+//    2.92 with two waves), width 1 also three (N = 500, L = 180, 2.9 / 3.0) and, from 768, four
+//    (N = 1000, L = 250, self-salt 3.28 / 3.43).  Chunks per pass: the most that pad a sequence
+//    by at most a sixth (N = 16384, L = 300, self-salt: 15.2 us with one chunk, 20.8 with 8;
+//    N = 4096, L = 512: 7.7 against 7.1 the other way), a third up to 2048 sequences, whose
+//    waves the chip holds at once (N = 2000, L = 400, self-salt: 5.9 us with one, 4.9 with 8).
+//  * Otherwise up to 16 waves share a sequence, as many as keep 8192 waves in all and one
+//    chunk each (from 512 sequences as few as leave each at most two: N = 1024, L = 512,
+//    self-salt 4.0 us, one each 4.2; L = 300, width 4, two or three each 4.7, at most two 4.3);
+//    two chunks a pass where a wave has them.  N = 128, L = 2048, self-salt width 4: 19.6 ->
+//    4.5 us.
 //  * Longer than 64 chunks, 8-wave workgroups split a sequence, splits^2 * N <= 2048:
 //    more splits cost more in adds to one slot than they save, and the zeroing launch
 //    costs about 2 us (N = 32, L = 4096: 5.1 us unsplit, 5.4 split; L = 16384: 122 -> 7.0).
@@ -2074,9 +2083,11 @@ template <int kSeeding, int kW>
 DetectPlan detect_plan(int64_t N, int64_t positions) {
   constexpr int kMaxChunk = kMaxDetectChunk<kSeeding, kW>;
   const int64_t chunks = (positions + kWave - 1) / kWave;
-  if (N > (kW == 1 ? 1024 : 2048) || chunks < 2) {
+  if (N > (kW == 1 ? 1024 : 2048) || chunks < 2 || (N >= 256 && chunks <= (kW == 1 ? 3 : 2)) ||
+      (kW == 1 && N >= 768 && chunks <= 4)) {
     int chunk = kMaxChunk;
-    while (chunk > 1 && ((chunks + chunk - 1) / chunk * chunk - chunks) * 8 > chunks) chunk /= 2;
+    const int64_t slack = N <= 2048 ? 3 : 6;
+    while (chunk > 1 && ((chunks + chunk - 1) / chunk * chunk - chunks) * slack > chunks) chunk /= 2;
     return DetectPlan{1, chunk, 0u};
   }
   DetectPlan p{kMaxSplitWaves, 1, 1u};
@@ -2084,8 +2095,8 @@ DetectPlan detect_plan(int64_t N, int64_t positions) {
     while (p.splits * 16 <= chunks && 4 * int64_t{p.splits} * p.splits * N <= 2048) p.splits *= 2;
     if (p.splits > 1u) p.waves = 8;
   }
-  const int64_t each = kMaxChunk > 1 && N >= 512 ? 2 : 1;   // chunks that a wave has at least
-  while (p.waves > 1 && (p.waves * N > 8192 || p.waves * each > chunks)) p.waves /= 2;
+  const int64_t each = kMaxChunk > 1 && N >= 512 ? 2 : 1;   // chunks that a wave has at most
+  while (p.waves > 1 && (p.waves * N > 8192 || p.waves / 2 * each >= chunks)) p.waves /= 2;
   if (kMaxChunk > 1 && 2 * p.waves * int64_t{p.splits} <= chunks) p.chunk = 2;
   return p;
 }
@@ -2125,7 +2136,8 @@ void launch_detect(int64_t positions, hipStream_t st, const int32_t* tokens, int
 // Threads of the workgroup that takes a text with the repeat rule: the most that its
 // positions keep busy while the launch stays within 4096 waves, as every text costs its waves'
 // launch, staging and barriers (about 1.6 waves start per ns); but enough for 24 waves a CU
-// where the texts' LDS lets only few workgroups share one.  us at 64 / 128 / 256 / 512 threads
+// where the texts' LDS lets only few workgroups share one, 16 up to 1024 texts, which leave a
+// CU four at most (1024 x 1040, context: 9.0 us, 9.7 with 512 threads).  us at 64 / 128 / 256 / 512 threads
 // (1024 for the last three): 4000 texts of 60 tokens 6.0 / 7.5 / 10.3 / 19.1; 4096 x 512 20.5 /
 // 15.2 / 16.1 / 21.3; 8000 x 1000 75 / 49 / 38 / 52; 1024 x 1024 25.1 / 15.3 / 11.0 / 11.7;
 // 512 x 512 11.4 / 7.4 / 5.7 / 5.1; 512 x 4096 140 / 81 / 45 / 31.7 (36); 256 x 1024 24.0 / 14.0 /
@@ -2134,7 +2146,8 @@ void launch_detect(int64_t positions, hipStream_t st, const int32_t* tokens, int
 int unique_block(int64_t N, int64_t positions, size_t lds) {
   int block = 64;
   while (block < 1024 && block < positions &&
-         (N * 2 * block <= 64 * 4096 || static_cast<size_t>(block) * 160 * 1024 < 64 * 24 * lds))
+         (N * 2 * block <= 64 * 4096 ||
+          static_cast<size_t>(block) * 160 * 1024 < 64 * (N > 1024 ? 24 : 16) * lds))
     block *= 2;
   return block;
 }

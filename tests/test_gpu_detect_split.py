@@ -3,8 +3,8 @@
 Few sequences are scored by up to 16 waves each, and sequences of more than 64 chunks of
 64 positions by several workgroups, whose counts meet in the sequence's z slot.  The
 cases sit on both sides of every line of that choice: one chunk and two, 64 chunks and 65,
-the batches at which fewer waves or splits are taken (and the first that takes one wave
-per sequence), a last pass that only some waves have, texts that end before a split's
+the batches at which fewer waves or splits are taken (and the first that take one wave
+per sequence, for two, three and four chunks), a last pass that only some waves have, texts that end before a split's
 first position.  Windows of 1, 2, 5 and 8 tokens share their hashed terms through LDS
 (self-salt) or not.  Counts and scored counts equal the oracle's, z within 1e-6 relative;
 every case runs twice on the same output buffers, so a slot left over from the first run
@@ -23,7 +23,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("seeding", ["context", "self_salt"])
 @pytest.mark.parametrize("width", [1, 2, 5, 8])
 @pytest.mark.parametrize("N,L", [(1, 72), (3, 137), (2, 4105), (2, 4300), (9, 4300), (33, 4170), (7, 16390),
-                                 (513, 260), (1025, 200), (2049, 75)])
+                                 (513, 260), (1025, 200), (2049, 75), (255, 130), (256, 130), (300, 180),
+                                 (767, 250), (768, 250), (1000, 300), (600, 600), (1500, 420)])
 def test_detect_split(env, seeding, width, N, L):
     torch, sbw, dev = env
     rng = np.random.default_rng(900 + width + N + L)
