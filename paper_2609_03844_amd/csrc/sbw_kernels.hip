@@ -48,15 +48,15 @@ namespace {
 #ifndef SBW_CONTEXT_UNROLL_BF16
 #define SBW_CONTEXT_UNROLL_BF16 2
 #endif
-// Self-salt, width 1: the split-term slab kernel.  fp32: 12-row slabs when that makes at
-// least SBW_SLAB12_MIN_GROUPS workgroups, else with 8-row, else with 6-row slabs when that
-// makes at least SBW_SLAB_MIN_GROUPS (below that its long-lived waves leave the chip
-// underfilled and the row kernel is faster).  12-row slabs need more workgroups than the
-// others: with fewer than ~1.7 rounds of the ~1800 that fit at once, the last round's tail
-// costs more than the shorter slabs' extra self terms.  bf16: 12-row slabs from
-// SBW_SLAB_BF16_MIN_GROUPS, B = 1024 of 152064 (6450 workgroups: 215 us, row kernel 228);
-// below the row kernel is at least as fast (B = 512, 3225: 116.1 / 115.7; B = 256:
-// 62.5 / 59.1; B = 128 of 128256: 32.0 / 27.7).
+// Self-salt, width 1: the split-term slab kernel.  12-row slabs when that makes at least
+// SBW_SLAB12_MIN_GROUPS workgroups, else with 8-row, else (fp32) with 6-row slabs when that
+// makes at least SBW_SLAB_MIN_GROUPS, bf16 SBW_SLAB_BF16_MIN_GROUPS (below that its
+// long-lived waves leave the chip underfilled and the row kernel is faster).  12-row slabs
+// need more workgroups than the others: with fewer than ~1.7 rounds of the ~1800 that fit at
+// once, the last round's tail costs more than the shorter slabs' extra self terms.  bf16 us,
+// slabs / row kernel: 12 rows, B = 700 of 152064 (4425 workgroups) 152 / 164, B = 512 (3225)
+// 117.1 / 118.2; 8 rows, B = 400 (3750) 89.1 / 91.6, B = 300 (2850) 69.1 / 72.3, B = 280 (2625)
+// 67.2 / 65.9, B = 256 (2400) 61.9 / 60.6.
 // Context seeding: launches of at least SBW_XCD_ROWS_MIN rows (a multiple of 8) and
 // SBW_XCD_ROWS_MIN_BYTES of logits, more than the 256 MB Infinity Cache holds, give
 // each XCD whole rows (fp32 B = 512 / 1024 of 152064: 1 / 3 % faster, bf16 B = 1024:
@@ -71,7 +71,7 @@ namespace {
 #define SBW_SLAB_MIN_GROUPS 2000
 #endif
 #ifndef SBW_SLAB_BF16_MIN_GROUPS
-#define SBW_SLAB_BF16_MIN_GROUPS 4800
+#define SBW_SLAB_BF16_MIN_GROUPS 2700
 #endif
 #ifndef SBW_SLAB12_MIN_GROUPS
 #define SBW_SLAB12_MIN_GROUPS 3000
@@ -1861,8 +1861,8 @@ void launch_watermark(void* logits, int64_t B, uint32_t V, int64_t row_stride,
       auto launch_slab = [&](auto height) -> bool {
         constexpr int kRows = decltype(height)::value;
         const int64_t slabs = (B + kRows - 1) / kRows;
-        const int64_t least = sizeof(T) == 2 ? SBW_SLAB_BF16_MIN_GROUPS
-                              : kRows == 12  ? SBW_SLAB12_MIN_GROUPS : SBW_SLAB_MIN_GROUPS;
+        const int64_t least = kRows == 12      ? SBW_SLAB12_MIN_GROUPS
+                              : sizeof(T) == 2 ? SBW_SLAB_BF16_MIN_GROUPS : SBW_SLAB_MIN_GROUPS;
         if (static_cast<int64_t>(tiles1) * slabs < least) return false;
         const dim3 grid(tiles1 + edge, static_cast<uint32_t>(slabs < kMaxGridY ? slabs : kMaxGridY));
         if (edge != 0u)
@@ -1874,8 +1874,8 @@ void launch_watermark(void* logits, int64_t B, uint32_t V, int64_t row_stride,
         return true;
       };
       if (launch_slab(std::integral_constant<int, 12>{})) return;
+      if (launch_slab(std::integral_constant<int, 8>{})) return;
       if constexpr (sizeof(T) == 4) {
-        if (launch_slab(std::integral_constant<int, 8>{})) return;
         if (launch_slab(std::integral_constant<int, 6>{})) return;
       }
     }

@@ -1,7 +1,7 @@
 """GPU parity of the self-salt split-term slab kernel (fp32 and bf16, window of one token).
 
 Large self-salt launches take a kernel that draws each column's self-term block once
-per slab of 12 rows (fp32: 8, then 6, for launches that taller slabs would leave with too
+per slab of 12 rows (8, then, fp32, 6 for launches that taller slabs would leave with too
 few workgroups) and queues in LDS only the (row, token) pairs whose row term is the
 smaller one.  Every case here is sized to take that kernel (the launch rule is
 mirrored in `slab_rows`, with its figures read from the kernel source, and asserted),
@@ -44,12 +44,14 @@ def slab_rows(B, V, dtype="f32", start=0):
     """The launch rule of the self-salt watermark, window of one token, for columns
     start .. start + V - 1: the slab height the launch takes, or 0 for the row kernel.  Tiles
     are of 256 whole 16-byte vectors whose first token id is a multiple of their tokens."""
+    if V <= 256:
+        return 0                          # one token per lane
     per = 4 if dtype == "f32" else 8
     head = min(-start % per, V)
     tiles = -(-((V - head) // per) // 256)
     heights = ([(12, knob("SBW_SLAB12_MIN_GROUPS")), (8, knob("SBW_SLAB_MIN_GROUPS")),
                 (6, knob("SBW_SLAB_MIN_GROUPS"))] if dtype == "f32"
-               else [(12, knob("SBW_SLAB_BF16_MIN_GROUPS"))])
+               else [(12, knob("SBW_SLAB12_MIN_GROUPS")), (8, knob("SBW_SLAB_BF16_MIN_GROUPS"))])
     for rows, least in heights:
         if tiles * -(-B // rows) >= least:
             return rows
@@ -144,13 +146,14 @@ def test_slab_shard(env):
 
 @pytest.mark.parametrize("dtype,B,n,start,rows,offset,pad", [
     ("f32", 2129, 16391, 57025, 12, 0, 0),    # 3 columns before the first vector, 4097 vectors
-    ("f32", 36003, 26, 1003, 12, 1, 3),       # one column before, one after; a slab of 3 rows
-    ("f32", 36001, 9, 2, 12, 0, 1),           # 2 before, 3 after, one vector
-    ("f32", 16005, 27, 1001, 8, 3, 2),        # 8-row slabs, a last one of 5 rows
+    ("f32", 36003, 258, 1003, 12, 1, 3),      # one column before, one after; a slab of 3 rows
+    ("f32", 36001, 261, 2, 12, 0, 1),         # 2 before, 3 after
+    ("f32", 16005, 307, 1001, 8, 3, 2),       # 8-row slabs, a last one of 5 rows
     ("f32", 12005, 1027, 6, 6, 2, 0),         # 6-row slabs, a last one of 5 rows, 256 vectors
-    ("bf16", 57605, 45, 57027, 12, 1, 4),     # 5 before, none after
-    ("bf16", 57600, 30, 9, 12, 0, 1),         # 7 before, 7 after
-    ("bf16", 28801, 2060, 4, 12, 3, 0),       # 4 before, 257 vectors
+    ("bf16", 36005, 301, 57027, 12, 1, 4),    # 5 before, none after
+    ("bf16", 36000, 270, 9, 12, 0, 1),        # 7 before, 7 after
+    ("bf16", 18001, 2060, 4, 12, 3, 0),       # 4 before, 257 vectors
+    ("bf16", 21605, 261, 2, 8, 1, 2),         # 8-row slabs, a last one of 5 rows; 6 before, 7 after
 ])
 def test_slab_shard_inside_a_vector(env, dtype, B, n, start, rows, offset, pad):
     """Shards whose first token id is not a multiple of a vector's tokens."""
@@ -180,16 +183,22 @@ def test_slab_twice_in_a_row(env):
 
 def test_slab_grid_stride(env):
     """More slabs than the 65535 workgroups of the grid's y dimension: some workgroups
-    take a second slab (and 800003 rows of 6 logits: a 2-logit row tail, a last slab of
-    11 rows)."""
-    B, V = 800003, 6
+    take a second slab (800003 rows of 258 logits: a 2-logit row tail, a last slab of 11
+    rows).  The oracle checks the first rows, those around the second slabs and the last."""
+    torch, sbw, dev = env
+    B, V = 800003, 258
     assert takes_slab(B, V) and -(-B // SLAB_ROWS) > 65535
     rng = np.random.default_rng(5150)
-    x = rng.standard_normal((B, V)).astype(np.float32)
+    x = torch.randn((B, V), generator=torch.Generator(device=dev).manual_seed(5150), device=dev)
     prev = rng.integers(0, 1 << 20, B).astype(np.int32)
+    second = 65000 * SLAB_ROWS
+    pick = np.r_[0:3000, second:second + 9000, B - 9000:B]
+    at = torch.from_numpy(pick).to(dev)
+    before = x[at].cpu().numpy()
     say(f"slab grid stride B={B} V={V}")
-    got, _ = run(env, x, prev, WIDE, 0.25, 2.0)
-    assert_logits_equal(got, oracle.watermark(x, prev, WIDE, 0.25, 2.0, "self_salt"), "grid stride")
+    sbw.watermark(x, torch.from_numpy(prev).to(dev), WIDE, 0.25, 2.0, "self_salt")
+    assert_logits_equal(x[at].cpu().numpy(), oracle.watermark(before, prev[pick], WIDE, 0.25, 2.0, "self_salt"),
+                        "grid stride")
 
 
 @pytest.mark.parametrize("B,V", [
@@ -226,15 +235,18 @@ def test_slab_six_rows(env, B, V):
                         f"B={B} V={V}")
 
 
-@pytest.mark.parametrize("B,V,stride,offset", [
-    (57601, 23, None, 0),      # 2 vectors, V mod 8 = 7, rows off 16 bytes, a last slab of 1 row
-    (57607, 40, 48, 0),        # whole vectors, padded aligned rows, a last slab of 7 rows
-    (28807, 2059, 2064, 0),    # 257 vectors (tile of 1), V mod 8 = 3, padded aligned rows
-    (28800, 2057, None, 3),    # the same off 16 bytes, whole slabs
+@pytest.mark.parametrize("B,V,stride,offset,rows", [
+    (36001, 263, None, 0, 12),      # V mod 8 = 7, rows off 16 bytes, a last slab of 1 row
+    (36007, 264, 272, 0, 12),       # whole vectors, padded aligned rows, a last slab of 7 rows
+    (18007, 2059, 2064, 0, 12),     # 257 vectors (tile of 1), V mod 8 = 3, padded aligned rows
+    (18000, 2057, None, 3, 12),     # the same off 16 bytes, whole slabs
+    (3600, 20483, None, 0, 12),     # 10 tiles
+    (21603, 264, None, 0, 8),       # 8-row slabs, a last one of 3 rows
+    (400, 152064, None, 0, 8),
 ])
-def test_slab_bf16(env, B, V, stride, offset):
+def test_slab_bf16(env, B, V, stride, offset, rows):
     """bf16 logits: 8 tokens a vector, two Philox counters a lane, 8 map bytes a row."""
-    assert slab_rows(B, V, "bf16") == 12
+    assert slab_rows(B, V, "bf16") == rows
     rng = np.random.default_rng(1616 + B + V)
     x = special_logits(rng, B, V, "bf16")
     prev = rng.integers(0, 1 << 31, B).astype(np.int32)
@@ -247,8 +259,8 @@ def test_slab_bf16(env, B, V, stride, offset):
 
 
 @pytest.mark.parametrize("B,V,stride", [
-    (3600, 20483, None),      # rows off 16 bytes, V mod 8 = 3
-    (3607, 20480, 20488),     # padded rows
+    (1600, 20483, None),      # rows off 16 bytes, V mod 8 = 3
+    (1607, 20480, 20488),     # padded rows
     (256, 152064, None),      # the c4 shape in bf16
     (263, 152061, 152064),    # V mod 8 = 5
     (192, 152064, None),
@@ -275,7 +287,7 @@ def test_bf16_below_the_slab_line(env, B, V, stride):
     (1.0, 4.0, WIDE),
 ])
 def test_slab_bf16_parameters(env, gamma, delta, key):
-    B, V = 57603, 101
+    B, V = 36003, 269
     assert slab_rows(B, V, "bf16") == 12
     rng = np.random.default_rng(int(gamma * 1e6) + int(delta * 10) + 7)
     x = special_logits(rng, B, V, "bf16")
@@ -288,7 +300,7 @@ def test_slab_bf16_parameters(env, gamma, delta, key):
 
 def test_slab_bf16_shard(env):
     """A bf16 vocabulary shard whose first token id is a multiple of 8 (not of 16)."""
-    a, n, V, B = 57024 + 8, 40, 152064, 57613
+    a, n, V, B = 57024 + 8, 264, 152064, 36013
     assert slab_rows(B, n, "bf16", a) == 12
     rng = np.random.default_rng(4343)
     x = workloads.f32_to_bf16_bits(rng.standard_normal((B, n)).astype(np.float32) * np.float32(2))
@@ -301,10 +313,11 @@ def test_slab_bf16_shard(env):
 def test_launch_rule_cases():
     """The c4 configurations take 12-row slabs, B = 160-240 of 152064 tokens and B = 128
     of 128256 8-row ones, B = 96 6-row ones; c3 and small batches take the row kernel.
-    bf16 takes slabs only at B = 1024."""
+    bf16 takes 12-row slabs from about B = 500, 8-row ones from about 300."""
     assert slab_rows(256, 152064) == 12 and slab_rows(1024, 152064) == 12
     assert slab_rows(160, 152064) == 8 and slab_rows(240, 152064) == 8
     assert slab_rows(128, 128256) == 8 and slab_rows(96, 128256) == 6
     assert slab_rows(64, 128256) == 0 and slab_rows(16, 152064) == 0
     assert slab_rows(1024, 152064, "bf16") == 12
-    assert slab_rows(512, 152064, "bf16") == 0 and slab_rows(256, 152064, "bf16") == 0
+    assert slab_rows(512, 152064, "bf16") == 12 and slab_rows(400, 152064, "bf16") == 8
+    assert slab_rows(256, 152064, "bf16") == 0
