@@ -8,7 +8,8 @@
 //             Context seeding shares one Philox block between the 4 tokens of a
 //             counter; self-salt needs one block per token, and its workgroups take
 //             several rows in turn with each candidate's hash and self term computed
-//             once.  Large self-salt launches (window of one token) instead draw each
+//             once.  Launches that leave the chip mostly idle take one token per
+//             lane instead.  Large self-salt launches (window of one token) instead draw each
 //             column's self-term block once per slab of 12, 8 or 6 rows and queue in
 //             LDS only the pairs whose row term is the smaller one (about half).
 // argmax      greedy decoding of the watermarked logits without writing them: one
@@ -82,6 +83,7 @@ constexpr int kMaxWidth = 8;             // longest context window
 constexpr int kMidWidth = 4;             // windows of 2-4 (the paper's 4): own instantiations
 constexpr int64_t kMaxGrid = 1ll << 20;  // blocks; grid-stride loops cover the rest
 constexpr int64_t kMaxGridY = 65535;
+constexpr int64_t kMaxEdgeY = 4096;      // grid rows of edge columns; a loop covers the rest
 
 // Native vector types (the non-temporal builtins take these, not HIP's float4/uint4).
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -256,36 +258,36 @@ __device__ __forceinline__ uint16_t bias_elem(uint16_t l, float d, bool g) {
   return bias_bf16(l, d, g);
 }
 
-// One token: column v of the row, token id vbase + v.
-template <typename T, int kSeeding, int kW>
-__device__ __forceinline__ void bias_one(T* row, uint32_t v, const RowSeed<kW>& rs, uint32_t tm1,
-                                         float delta, uint32_t vbase) {
-  const uint32_t x = draw<kSeeding>(rs, vbase + v);
-  row[v] = bias_elem(row[v], delta, is_green(x, tm1));
-}
-
-// The columns outside whole vectors (RowSplit): the last workgroup column of a launch that
-// has any takes them, one lane a column, 16 rows a workgroup.  A path of its own, so that
-// the tiles' path keeps no registers for it (inside the tiles it cost 2-13 VGPRs a lane
-// and with them a wave per SIMD: bf16 self-salt 256 x 152064, width 4, 96 -> 106 us).
+// The columns outside whole vectors (RowSplit), one lane a column, 16 rows a workgroup: the
+// workgroups of a launch's last `edge_y` grid rows take them, after the tiles'.  A path of its
+// own, so that the tiles' path keeps no registers for it (inside the tiles it cost 2-13 VGPRs
+// a lane and with them a wave per SIMD: bf16 self-salt 256 x 152064, width 4, 96 -> 106 us),
+// and only as many workgroups as have work: a column of one per row, most of them empty, cost
+// their dispatch (1000 x 2001 fp32, self-salt: 9.5 us, 6.6 so; 500 x 32001 bf16, 32.0, 28.4).
+// In front of the tiles they delay these (48 x 128259 bf16, self-salt: 14.3 us, 13.3 behind).
+__device__ __forceinline__ uint32_t tile_rows(uint32_t edge_y) { return gridDim.y - edge_y; }
 constexpr uint32_t kEdgeRows = 16;
 static_assert(kThreads / kEdgeRows >= 14, "a row has at most 7 + 7 such columns");
 template <typename T, int kSeeding, int kW, uint32_t kPer>
 __device__ __forceinline__ void watermark_edges(T* logits, int64_t row_stride, const RowSplit& sp,
                                                 int64_t B, const int32_t* context, int width,
                                                 uint64_t key, uint32_t tm1, float delta,
-                                                uint32_t vbase, int64_t slot) {
+                                                uint32_t vbase, uint32_t edge_y) {
+  const int64_t slot = static_cast<int64_t>(blockIdx.y - tile_rows(edge_y)) * gridDim.x + blockIdx.x;
   const uint32_t e = threadIdx.x % (kThreads / kEdgeRows);
   if (e >= sp.edges()) return;
   for (int64_t row = slot * kEdgeRows + threadIdx.x / (kThreads / kEdgeRows); row < B;
-       row += static_cast<int64_t>(gridDim.y) * kEdgeRows) {
+       row += static_cast<int64_t>(edge_y) * gridDim.x * kEdgeRows) {
+    // the logit is on its way while the window is read and the colour drawn
+    T* p = logits + row * row_stride + sp.edge<kPer>(e);
+    const T l = *p;
     const RowSeed<kW> rs = row_seed<kSeeding, kW>(key, context + row * width, width);
-    bias_one<T, kSeeding>(logits + row * row_stride, sp.edge<kPer>(e), rs, tm1, delta, vbase);
+    *p = bias_elem(l, delta, is_green(draw<kSeeding>(rs, vbase + sp.edge<kPer>(e)), tm1));
   }
 }
 
-// Context-seeded watermark.  Grid: x = tile of kThreads * kU vectors within a row, y = row (grid-stride over rows beyond
-// 65535).  Each lane issues its logits load before reading the row's window, so the
+// Context-seeded watermark.  Grid: x = tile of kThreads * kU vectors within a row, y = row
+// (grid-stride over rows beyond 65535), then edge_y rows for the edge columns.  Each lane issues its logits load before reading the row's window, so the
 // scalar loads of the window overlap the HBM stream.  With xcd_rows (one row per y,
 // B a multiple of 8) the workgroups are renumbered so that each of the 8 XCDs, which
 // take workgroups in turn, streams whole rows: workgroup n goes to row
@@ -294,13 +296,18 @@ template <typename T, int kU, int kW>
 __global__ void __launch_bounds__(kThreads)
 watermark_vec_kernel(T* __restrict__ logits, int64_t row_stride, uint32_t V, int64_t B,
                      const int32_t* __restrict__ context, int width, uint64_t key, uint32_t tm1,
-                     float delta, uint32_t vbase, uint32_t xcd_rows) {
+                     float delta, uint32_t vbase, uint32_t xcd_rows, uint32_t edge_y) {
   using VecT = typename VecOf<T>::Value;
   using MemT = typename VecOf<T>::Memory;
   constexpr uint32_t kPer = 16u / sizeof(T);  // elements per 16-byte vector
   const RowSplit sp = row_split<kPer>(V, vbase);
   const uint32_t full = sp.full;
   const uint32_t jbase = sp.id;
+  if (blockIdx.y >= tile_rows(edge_y)) {
+    watermark_edges<T, kContext, kW, kPer>(logits, row_stride, sp, B, context, width, key, tm1, delta, vbase,
+                                           edge_y);
+    return;
+  }
   uint32_t first = blockIdx.x * (kThreads * kU);
   int64_t row0 = blockIdx.y;
   if (xcd_rows != 0u) {
@@ -309,12 +316,7 @@ watermark_vec_kernel(T* __restrict__ logits, int64_t row_stride, uint32_t V, int
     row0 = static_cast<int64_t>(q / gridDim.x) * 8 + (n & 7u);
     first = (q % gridDim.x) * (kThreads * kU);
   }
-  if (first >= full) {   // the workgroup column after the tiles
-    watermark_edges<T, kContext, kW, kPer>(logits, row_stride, sp, B, context, width, key, tm1, delta, vbase,
-                                     row0);
-    return;
-  }
-  for (int64_t row = row0; row < B; row += gridDim.y) {
+  for (int64_t row = row0; row < B; row += tile_rows(edge_y)) {
     MemT* vec = reinterpret_cast<MemT*>(logits + row * row_stride + sp.head);
     const int32_t* window = context + row * width;
     VecT buf[kU];
@@ -344,6 +346,26 @@ watermark_vec_kernel(T* __restrict__ logits, int64_t row_stride, uint32_t V, int
   }
 }
 
+// One token per lane, one row per y, either seeding, any start.  For launches that leave the
+// chip mostly idle, where the time is that of a lane's chain of instructions: a vector's
+// four or eight tokens lengthen it, and the workgroup column for the edges of a row that has
+// some adds 0.3-0.5 us (16 x 4001 fp32, context: 2.25 us, 2.88 with vectors; 1 x 32000: 2.04,
+// 2.23; self-salt width 4 2.29, 2.64).
+template <typename T, int kSeeding, int kW>
+__global__ void __launch_bounds__(kThreads)
+watermark_token_kernel(T* __restrict__ logits, int64_t row_stride, uint32_t V,
+                       int64_t B, const int32_t* __restrict__ context, int width, uint64_t key,
+                       uint32_t tm1, float delta, uint32_t vbase) {
+  const uint32_t v = blockIdx.x * blockDim.x + threadIdx.x;
+  if (v >= V) return;
+  for (int64_t row = blockIdx.y; row < B; row += gridDim.y) {
+    T* p = logits + row * row_stride + v;
+    const T l = *p;
+    const RowSeed<kW> rs = row_seed<kSeeding, kW>(key, context + row * width, width);
+    *p = bias_elem(l, delta, is_green(draw<kSeeding>(rs, vbase + v), tm1));
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Self-salt watermark.  The rows of a workgroup share their columns, so a candidate's J(v)
 // and the row-independent term key*J(v)*J(v) of its seed are computed once per lane and
@@ -367,8 +389,8 @@ __device__ __forceinline__ u32x2 bias_quad(u32x2 l, const uint32_t (&x)[4], uint
                bias_bf16x2(l.y, delta, is_green(x[2], tm1), is_green(x[3], tm1))};
 }
 
-// Grid: x = tile of kThreads * kU quads of a row, y = a slot that takes the rows y,
-// y + gridDim.y, ...  The candidate terms depend on the columns only, so a workgroup
+// Grid: x = tile of kThreads * kU quads of a row, y = a slot that takes the rows y, y + the
+// number of slots, ...; then edge_y rows for the edge columns.  The candidate terms depend on the columns only, so a workgroup
 // computes them once, while its first row's loads are in flight, and uses them for every
 // row it takes.  Bound by VALU issue: at width 4 a logit costs about 75 instructions, 51
 // of them its Philox block.  The window is a template parameter, so the minimum is a
@@ -382,7 +404,7 @@ template <typename T, int kU, int kW>
 __global__ void __launch_bounds__(kThreads)
 watermark_ss_rows_kernel(T* __restrict__ logits, int64_t row_stride, uint32_t V, int64_t B,
                          const int32_t* __restrict__ context, uint64_t key, uint32_t tm1, float delta,
-                         uint32_t vbase) {
+                         uint32_t vbase, uint32_t edge_y) {
   using QuadT = typename QuadOf<T>::Value;
   using MemT = typename QuadOf<T>::Memory;
   const RowSplit sp = row_split<4>(V, vbase);
@@ -390,14 +412,13 @@ watermark_ss_rows_kernel(T* __restrict__ logits, int64_t row_stride, uint32_t V,
   const uint32_t first = blockIdx.x * (kThreads * kU);
   const uint32_t id_first = first + sp.id;   // the tile's first quad counted in token ids
   const bool whole = first + kThreads * kU <= full;
-  if (first >= full) {   // the workgroup column after the tiles
-    watermark_edges<T, kSelfSalt, kW, 4>(logits, row_stride, sp, B, context, kW, key, tm1, delta, vbase,
-                                         blockIdx.y);
+  if (blockIdx.y >= tile_rows(edge_y)) {
+    watermark_edges<T, kSelfSalt, kW, 4>(logits, row_stride, sp, B, context, kW, key, tm1, delta, vbase, edge_y);
     return;
   }
   CandTerm ct[kU][4];
   bool have_terms = false;
-  for (int64_t row = blockIdx.y; row < B; row += gridDim.y) {
+  for (int64_t row = blockIdx.y; row < B; row += tile_rows(edge_y)) {
     MemT* quads = reinterpret_cast<MemT*>(logits + row * row_stride + sp.head);
     QuadT buf[kU];
 #pragma unroll
@@ -602,7 +623,7 @@ __device__ __forceinline__ void slab_positions(SlabLds<kRows, kPer>& s, int rows
 }
 
 // Grid: x = tile of kThreads vectors (4 waves of 256 vectors), y = a slot taking the
-// slabs y, y + gridDim.y, ... of kRows rows.  T: float (4 tokens a vector) or bf16
+// slabs y, y + the number of slots, ... of kRows rows; then edge_y rows for the edges.  T: float (4 tokens a vector) or bf16
 // bits (8).  Rows of whole vectors have an instantiation of their own (kEdges false): the
 // path of the other columns in front of the tiles cost every wave its test and 0.8 %
 // (256 x 152064 fp32: 64.9 us without it, 65.5 with; 1024: 237.1 / 238.7).
@@ -610,7 +631,7 @@ template <typename T, int kRows, bool kEdges>
 __global__ void __launch_bounds__(kThreads)
 watermark_ss_slab_kernel(T* __restrict__ logits, int64_t row_stride, uint32_t V, int64_t B,
                          const int32_t* __restrict__ context, uint64_t key, uint32_t tm1,
-                         float delta, uint32_t vbase) {
+                         float delta, uint32_t vbase, uint32_t edge_y) {
   using VecT = typename VecOf<T>::Value;
   using MemT = typename VecOf<T>::Memory;
   constexpr int kPer = 16 / sizeof(T);  // tokens a vector
@@ -621,11 +642,11 @@ watermark_ss_slab_kernel(T* __restrict__ logits, int64_t row_stride, uint32_t V,
   SlabLds<kRows, kPer>& s = lds[wave];
   const RowSplit sp = kEdges ? row_split<kPer>(V, vbase) : RowSplit{0u, V / kPer, 0u, vbase / kPer};
   const uint32_t full = sp.full;
-  if (kEdges && blockIdx.x * kThreads >= full) {   // the workgroup column after the tiles
-    watermark_edges<T, kSelfSalt, 1, kPer>(logits, row_stride, sp, B, context, 1, key, tm1, delta, vbase,
-                                     blockIdx.y);
+  if (kEdges && blockIdx.y >= tile_rows(edge_y)) {
+    watermark_edges<T, kSelfSalt, 1, kPer>(logits, row_stride, sp, B, context, 1, key, tm1, delta, vbase, edge_y);
     return;
   }
+  const uint32_t slots = kEdges ? tile_rows(edge_y) : gridDim.y;
   const uint32_t j0 = blockIdx.x * kThreads + wave * 64u;  // the wave's first vector
   const uint32_t j = j0 + lane;
   const bool active = j < full;
@@ -656,7 +677,7 @@ watermark_ss_slab_kernel(T* __restrict__ logits, int64_t row_stride, uint32_t V,
   }
   T* first_vec = logits + sp.head;
   const int64_t slabs = (B + kRows - 1) / kRows;
-  for (int64_t g = blockIdx.y; g < slabs; g += gridDim.y) {
+  for (int64_t g = blockIdx.y; g < slabs; g += slots) {
     const int64_t row0 = g * kRows;
     const int rows = static_cast<int>(B - row0 < kRows ? B - row0 : kRows);
     // step 1: the self decisions for every row, and each row's key * J(p)
@@ -1845,16 +1866,50 @@ int64_t rows_per_slot(int64_t tiles, int64_t B) {
   return best;
 }
 
+// Whether a launch takes one token per lane: rows of at most a workgroup's lanes, where vectors
+// would leave most of it idle (5000 x 100 fp32, context: 4.7 us, 6.7 with vectors), and small
+// launches.  The lines for these, where the two cross: rows of whole vectors 256K logits, fewer
+// with the wider windows of self-salt, whose shared terms are worth more (context fp32 256K
+// logits 2.25-2.34 us, vectors 2.32, 384K 2.5 / 2.4; self-salt width 2 192K 2.5 / 2.55, 256K
+// 2.7 / 2.6; width 4 128K 2.55 / 2.72, 192K 2.83 / 2.78; width 8 128K 3.1 / 3.1).  Rows with edge
+// columns, whose workgroups cost vectors about 0.5 us: context 300K 2.9-3.0 / 2.93-3.07, 400K
+// 3.1-3.3 / 3.0-3.1; width 1 400K 3.3 / 3.5, 500K 3.8 / 3.6; width 2 400K 3.6 / 3.6; width 4 300K
+// 3.7 / 3.7; width 8 150K 3.86 / 3.90, 200K 4.2 / 3.9; twice as many where such a row is shorter
+// than a tile (1300 x 301, width 1: 4.0 / 5.2; 1000 x 401, width 4: 4.6 / 5.1).
+template <int kSeeding, int kW>
+bool one_token_a_lane(int64_t B, uint32_t V, bool edges) {
+  constexpr int64_t kWhole = kSeeding == kContext || kW == 1 ? 8 : kW == 2 ? 6 : kW <= kMidWidth ? 5 : 4;
+  constexpr int64_t kEdges = kSeeding == kContext ? 10 : kW == 1 ? 13 : kW == 2 ? 12 : kW <= kMidWidth ? 9 : 5;
+  const int64_t most = edges ? kEdges << (V <= 2 * kThreads ? 16 : 15) : kWhole << 15;
+  return V <= kThreads || B <= most / V;
+}
+
 template <typename T, int kSeeding, int kW>
 void launch_watermark(void* logits, int64_t B, uint32_t V, int64_t row_stride,
                       const int32_t* context, int width, uint64_t key, uint32_t tm1, float delta,
                       uint32_t vbase, hipStream_t stream) {
   T* p = static_cast<T*>(logits);
   const uint32_t rows = static_cast<uint32_t>(B < kMaxGridY ? B : kMaxGridY);
+  const RowSplit split = row_split<kSeeding == kSelfSalt ? 4u : 16u / sizeof(T)>(V, vbase);
+  if (one_token_a_lane<kSeeding, kW>(B, V, split.head + split.tail != 0u)) {
+    const uint32_t threads = V < kThreads ? (V + 63u) / 64u * 64u : kThreads;
+    hipLaunchKernelGGL((watermark_token_kernel<T, kSeeding, kW>), dim3((V + threads - 1) / threads, rows),
+                       dim3(threads), 0, stream, p, row_stride, V, B, context, width, key, tm1, delta, vbase);
+    return;
+  }
   constexpr uint32_t kPer = 16u / sizeof(T);
   const RowSplit sp = row_split<kPer>(V, vbase);
   const uint64_t vectors = sp.full;
-  const uint32_t edge = sp.head + sp.tail != 0u ? 1u : 0u;   // a workgroup column for the edges
+  // grid rows for the edge columns, and the rows of the grid with `slots` of them for the tiles
+  auto edge_rows = [&](const RowSplit& r, uint32_t tiles) -> uint32_t {
+    if (r.head + r.tail == 0u) return 0u;
+    const int64_t groups = (B + kEdgeRows - 1) / kEdgeRows;
+    const int64_t y = (groups + tiles - 1) / tiles;
+    return static_cast<uint32_t>(y < kMaxEdgeY ? y : kMaxEdgeY);
+  };
+  auto grid_y = [&](int64_t slots, uint32_t edge_y) {
+    return static_cast<uint32_t>(slots < kMaxGridY - edge_y ? slots : kMaxGridY - edge_y) + edge_y;
+  };
   if constexpr (kSeeding == kSelfSalt) {
     if constexpr (kW == 1) {
       const uint32_t tiles1 = static_cast<uint32_t>((vectors + kThreads - 1) / kThreads);
@@ -1864,13 +1919,14 @@ void launch_watermark(void* logits, int64_t B, uint32_t V, int64_t row_stride,
         const int64_t least = kRows == 12      ? SBW_SLAB12_MIN_GROUPS
                               : sizeof(T) == 2 ? SBW_SLAB_BF16_MIN_GROUPS : SBW_SLAB_MIN_GROUPS;
         if (static_cast<int64_t>(tiles1) * slabs < least) return false;
-        const dim3 grid(tiles1 + edge, static_cast<uint32_t>(slabs < kMaxGridY ? slabs : kMaxGridY));
-        if (edge != 0u)
+        const uint32_t edge_y = edge_rows(sp, tiles1);
+        const dim3 grid(tiles1, grid_y(slabs, edge_y));
+        if (edge_y != 0u)
           hipLaunchKernelGGL((watermark_ss_slab_kernel<T, kRows, true>), grid, dim3(kThreads), 0, stream, p,
-                             row_stride, V, B, context, key, tm1, delta, vbase);
+                             row_stride, V, B, context, key, tm1, delta, vbase, edge_y);
         else
           hipLaunchKernelGGL((watermark_ss_slab_kernel<T, kRows, false>), grid, dim3(kThreads), 0, stream, p,
-                             row_stride, V, B, context, key, tm1, delta, vbase);
+                             row_stride, V, B, context, key, tm1, delta, vbase, 0u);
         return true;
       };
       if (launch_slab(std::integral_constant<int, 12>{})) return;
@@ -1880,33 +1936,34 @@ void launch_watermark(void* logits, int64_t B, uint32_t V, int64_t row_stride,
       }
     }
     const RowSplit quads = row_split<4>(V, vbase);
-    const uint32_t quad_edge = quads.head + quads.tail != 0u ? 1u : 0u;
     const uint32_t tiles2 = (quads.full + 2 * kThreads - 1) / (2 * kThreads);
     if (tiles2 * B < kTwoQuadMinGroups) {
-      const dim3 grid((quads.full + kThreads - 1) / kThreads + quad_edge, rows);
-      hipLaunchKernelGGL((watermark_ss_rows_kernel<T, 1, kW>), grid, dim3(kThreads), 0, stream, p,
-                         row_stride, V, B, context, key, tm1, delta, vbase);
+      const uint32_t tiles = (quads.full + kThreads - 1) / kThreads;
+      const uint32_t edge_y = edge_rows(quads, tiles);
+      hipLaunchKernelGGL((watermark_ss_rows_kernel<T, 1, kW>), dim3(tiles, grid_y(B, edge_y)), dim3(kThreads),
+                         0, stream, p, row_stride, V, B, context, key, tm1, delta, vbase, edge_y);
       return;
     }
     const int64_t slots = (B + rows_per_slot(tiles2, B) - 1) / rows_per_slot(tiles2, B);
-    const dim3 grid(tiles2 + quad_edge, static_cast<uint32_t>(slots < kMaxGridY ? slots : kMaxGridY));
-    hipLaunchKernelGGL((watermark_ss_rows_kernel<T, 2, kW>), grid, dim3(kThreads), 0, stream, p,
-                       row_stride, V, B, context, key, tm1, delta, vbase);
+    const uint32_t edge_y = edge_rows(quads, tiles2);
+    hipLaunchKernelGGL((watermark_ss_rows_kernel<T, 2, kW>), dim3(tiles2, grid_y(slots, edge_y)),
+                       dim3(kThreads), 0, stream, p, row_stride, V, B, context, key, tm1, delta, vbase, edge_y);
   } else {
     // Two vectors in flight per lane measured best (~80 % of HBM peak; one: ~75 %).
     constexpr int kU = sizeof(T) == 4 ? SBW_CONTEXT_UNROLL : SBW_CONTEXT_UNROLL_BF16;
     const uint32_t tiles = static_cast<uint32_t>((vectors + kThreads * kU - 1) / (kThreads * kU));
     // whole rows per XCD for large launches (one launch row per grid row, workgroup
     // numbers below 2^32)
+    const uint32_t edge_y = edge_rows(sp, tiles);
     const uint32_t xcd_rows =
-        B >= SBW_XCD_ROWS_MIN && B % 8 == 0 && B <= kMaxGridY &&
+        B >= SBW_XCD_ROWS_MIN && B % 8 == 0 && B <= kMaxGridY - edge_y &&
                 B * static_cast<int64_t>(V) * static_cast<int64_t>(sizeof(T)) >= SBW_XCD_ROWS_MIN_BYTES &&
-                (uint64_t{tiles} + edge) * static_cast<uint64_t>(B) < (uint64_t{1} << 32)
+                uint64_t{tiles} * static_cast<uint64_t>(B) < (uint64_t{1} << 32)
             ? 1u
             : 0u;
-    hipLaunchKernelGGL((watermark_vec_kernel<T, kU, kW>), dim3(tiles + edge, rows),
+    hipLaunchKernelGGL((watermark_vec_kernel<T, kU, kW>), dim3(tiles, grid_y(B, edge_y)),
                        dim3(kThreads), 0, stream, p, row_stride, V, B, context, width, key, tm1,
-                       delta, vbase, xcd_rows);
+                       delta, vbase, xcd_rows, edge_y);
   }
 }
 

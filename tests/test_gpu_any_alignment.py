@@ -2,11 +2,12 @@
 
 Logits move in 16-byte vectors (self-salt: 4-token quads) from any element address, with
 the columns before the first whole Philox block and after the last one taken one by one.
-The cases cover every start modulo 8 of a shard, rows shorter than a vector, rows one
-column either side of whole vectors and tiles, odd row strides and base offsets, windows of
-1-8 tokens (each its own self-salt kernel), one and two quads per lane, and workgroups that
-take several rows.  Logits bit for bit against the oracle, and nothing outside the shard's
-columns may change.
+Small launches, and rows of at most 256 columns, take one token per lane.  The cases cover
+every start modulo 8 of a shard, rows shorter than a vector, rows one column either side of
+whole vectors and tiles, odd row strides and base offsets, windows of 1-8 tokens (each its
+own self-salt kernel), one and two quads per lane, workgroups that take several rows, and
+both sides of the lines between one token per lane and vectors.  Logits bit for bit against
+the oracle, and nothing outside the shard's columns may change.
 """
 import numpy as np
 import pytest
@@ -58,10 +59,37 @@ def test_every_start_and_short_rows(env, dtype, seeding, width):
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("seeding", ["context", "self_salt"])
+@pytest.mark.parametrize("width", [1, 3, 8])
+def test_every_start_with_vectors(env, dtype, seeding, width):
+    """Rows of more than 256 columns, more logits than one token per lane takes."""
+    for start in range(9):
+        for n in (1027, 4101):
+            check(env, dtype, seeding, width, 440000 // n, start, n, offset=start % 3, pad=n % 4)
+    for start, n in ((0, 257), (3, 263), (5, 511)):
+        check(env, dtype, seeding, width, 860000 // n, start, n, offset=1, pad=1)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("seeding,width,whole,edges", [
+    ("context", 4, 8 << 15, 10 << 15), ("self_salt", 1, 8 << 15, 13 << 15), ("self_salt", 2, 6 << 15, 12 << 15),
+    ("self_salt", 4, 5 << 15, 9 << 15), ("self_salt", 5, 4 << 15, 5 << 15)])
+def test_either_side_of_one_token_per_lane(env, dtype, seeding, width, whole, edges):
+    """The launches on both sides of each line: most logits of rows of whole vectors, of rows
+    with edge columns and of such rows of at most 512 columns; rows of 256 and 257 columns."""
+    for n, most in ((1024, whole), (1023, edges), (511, 2 * edges)):
+        for B in (most // n, most // n + 1):
+            check(env, dtype, seeding, width, B, 0, n, pad=0 if n == 1024 else 1)
+    for n in (255, 256, 257):
+        check(env, dtype, seeding, width, 4000, 1, n)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("seeding", ["context", "self_salt"])
 @pytest.mark.parametrize("n", [4095, 4096, 4097, 8191, 8193])
 def test_tile_edges(env, dtype, seeding, n):
     for start, offset, pad in [(0, 0, 0), (0, 1, 1), (1003, 0, 3), (1004, 5, 0)]:
-        check(env, dtype, seeding, 2, 37, start, n, offset, pad)
+        for B in (37, 110):                  # one token per lane, or vectors; vectors
+            check(env, dtype, seeding, 2, B, start, n, offset, pad)
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
@@ -72,8 +100,8 @@ def test_self_salt_rows_in_turn(env, dtype, width):
     check(env, dtype, "self_salt", width, 143, 1025, 10241, offset=1, pad=2, delta=-1.5)
 
 
-def test_bf16_slab_from_its_line(env):
-    """bf16, window of one token: 12-row slabs from 4800 of them (here 10 tiles x 501)."""
+def test_bf16_slab(env):
+    """bf16, window of one token: 12-row slabs (10 tiles x 501 workgroups)."""
     check(env, "bf16", "self_salt", 1, 6005, 0, 20477, pad=2)
 
 

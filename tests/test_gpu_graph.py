@@ -13,13 +13,14 @@ import workloads
 pytestmark = pytest.mark.gpu
 
 
-def test_graph_replays_match_eager_and_oracle():
+@pytest.mark.parametrize("B,V,N,L", [(8, 40003, 64, 300), (12, 40003, 3, 9000)])
+def test_graph_replays_match_eager_and_oracle(B, V, N, L):
+    """Small launches; then vectors, and texts that several workgroups share."""
     import torch
     import paper_2609_03844_amd as sbw
     dev = torch.device("cuda:0")
     key, gamma, delta = workloads.PAPER_KEY, 0.25, 2.0
     rng = np.random.default_rng(314)
-    B, V, N, L = 8, 40003, 64, 300
     x = rng.standard_normal((B, V)).astype(np.float32)
     prev = rng.integers(0, V, B).astype(np.int32)
     tok = rng.integers(0, V, (N, L)).astype(np.int32)

@@ -1,7 +1,8 @@
 """GPU parity when rows (or row groups) outnumber the 65535 workgroups of a grid's y
 dimension, so every row-parallel kernel runs its grid-stride loop: many short rows
 for the watermark (both seedings; self-salt through the slab kernel with a window of
-one token and through the row kernel with a window of 4), greedy decoding,
+one token and through the row kernel with a window of 4; rows of at most 256 logits take
+one token per lane, and those of at most 640 one decoding launch), greedy decoding,
 sampling, candidates and both detection kernels."""
 import numpy as np
 import pytest
@@ -15,7 +16,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("seeding", ["context", "self_salt"])
-@pytest.mark.parametrize("B,V", [(70001, 37), (300001, 8)])
+@pytest.mark.parametrize("B,V", [(70001, 37), (300001, 8), (66001, 261)])
 def test_watermark_many_rows(env, seeding, B, V):
     torch, sbw, dev = env
     rng = np.random.default_rng(240 + V)
@@ -29,11 +30,15 @@ def test_watermark_many_rows(env, seeding, B, V):
 
 
 def test_watermark_window_many_rows(env):
-    """Self-salt with a window of 4: 70001 rows of 40 logits run the row kernel's
-    grid-stride loop."""
+    """Self-salt with a window of 4: 70001 rows of 40 logits run the token kernel's
+    grid-stride loop, and of 261 the row kernel's slots of several rows."""
+    for V in (40, 261):
+        many_rows_with_a_window(env, 70001, V)
+
+
+def many_rows_with_a_window(env, B, V):
     torch, sbw, dev = env
     rng = np.random.default_rng(245)
-    B, V = 70001, 40
     x = rng.standard_normal((B, V)).astype(np.float32)
     ctx = workloads.context_tokens(B, 4, V, rng)
     say(f"watermark many rows, window 4, B={B} V={V}")
@@ -41,6 +46,30 @@ def test_watermark_window_many_rows(env):
     sbw.watermark(t, torch.from_numpy(ctx).to(dev), WIDE, 0.5, 1.5, "self_salt")
     torch.cuda.synchronize()
     assert_logits_equal(_from_device(torch, t), oracle.watermark_w(x, ctx, WIDE, 0.5, 1.5, "self_salt"))
+
+
+@pytest.mark.parametrize("sample", [False, True])
+def test_decode_segments_many_rows(env, sample):
+    """70001 rows of 641 logits, one more than the decoding of short rows takes; the oracle
+    checks the first rows, those that a workgroup takes second, and the last."""
+    torch, sbw, dev = env
+    rng = np.random.default_rng(251)
+    B, V = 70001, 641
+    x = torch.randn((B, V), generator=torch.Generator(device=dev).manual_seed(251), device=dev)
+    ctx = workloads.context_tokens(B, 4, V, rng)
+    seeds = rng.integers(0, 2**63, B, dtype=np.int64)
+    pick = np.r_[0:2000, 65000:67000, B - 1000:B]
+    say(f"decode segments many rows sample={sample}")
+    c, host = torch.from_numpy(ctx).to(dev), x[torch.from_numpy(pick).to(dev)].cpu().numpy()
+    if sample:
+        got = sbw.watermark_sample(x, c, WIDE, 0.5, 1.5, torch.from_numpy(seeds).to(dev), "self_salt", 0.9)
+        expect = oracle.watermark_sample(host, ctx[pick], WIDE, 0.5, 1.5, "self_salt",
+                                         seeds[pick].view(np.uint64), 0.9)
+    else:
+        got = sbw.watermark_argmax(x, c, WIDE, 0.5, 1.5, "self_salt")
+        expect = oracle.watermark_argmax(host, ctx[pick], WIDE, 0.5, 1.5, "self_salt")
+    assert np.array_equal(got[0].cpu().numpy()[pick], expect[0])
+    assert np.array_equal(got[1].cpu().numpy()[pick].view(np.uint32), expect[1].view(np.uint32))
 
 
 @pytest.mark.parametrize("seeding", ["context", "self_salt"])

@@ -134,8 +134,9 @@ def special_logits(rng, B, V, dtype):
 
 # --- small cases: tiles, ragged tails, layouts, special values ----------------------
 
+# The last three have more logits than the launches that take one token per lane.
 SHAPES = [(1, 1), (1, 3), (2, 5), (3, 31), (2, 32), (2, 33), (4, 1000), (3, 4097), (2, 32001),
-          (5, 1024 * 4 * 2 + 7)]
+          (5, 1024 * 4 * 2 + 7), (110, 4097), (15, 32001), (900, 1000)]
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
@@ -159,13 +160,13 @@ def test_watermark_small(env, dtype, seeding, B, V):
 def test_watermark_layouts(env, dtype, seeding, stride_pad, offset):
     # padded rows, rows off 16 bytes and aligned-but-offset starts, all with a 3-token row
     # tail; strides of 5008 and 5016 keep rows 16-byte aligned in both dtypes
-    rng = np.random.default_rng(77 + stride_pad * 10 + offset)
-    B, V = 6, 5003
-    x = special_logits(rng, B, V, dtype)
-    prev = rng.integers(0, V, B).astype(np.int32)
-    say(f"layout {dtype} {seeding} stride=V+{stride_pad} offset={offset}")
-    got = run_watermark(env, x, prev, KEY, 0.25, 2.0, seeding, stride=V + stride_pad, offset=offset)
-    assert_logits_equal(got, oracle.watermark(x, prev, KEY, 0.25, 2.0, seeding))
+    for B, V in ((6, 5003), (90, 5003)):     # one token per lane; vectors
+        rng = np.random.default_rng(77 + stride_pad * 10 + offset)
+        x = special_logits(rng, B, V, dtype)
+        prev = rng.integers(0, V, B).astype(np.int32)
+        say(f"layout {dtype} {seeding} B={B} stride=V+{stride_pad} offset={offset}")
+        got = run_watermark(env, x, prev, KEY, 0.25, 2.0, seeding, stride=V + stride_pad, offset=offset)
+        assert_logits_equal(got, oracle.watermark(x, prev, KEY, 0.25, 2.0, seeding))
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
@@ -173,14 +174,14 @@ def test_watermark_layouts(env, dtype, seeding, stride_pad, offset):
                                          (0.25, 3e38), (0.25, -3e38), (0.25, 1e-45),
                                          (5e-324, 1.0), (0.9999999999, 1.0)])
 def test_watermark_degenerate_parameters(env, dtype, gamma, delta):
-    rng = np.random.default_rng(5)
-    B, V = 3, 2051
-    x = special_logits(rng, B, V, dtype)
-    prev = np.array([0, -1, 2 ** 31 - 1], dtype=np.int32)  # 0, 0xFFFFFFFF, ids >= V
-    for seeding in ("context", "self_salt"):
-        say(f"degenerate {dtype} {seeding} gamma={gamma} delta={delta}")
-        got = run_watermark(env, x, prev, WIDE, gamma, delta, seeding)
-        assert_logits_equal(got, oracle.watermark(x, prev, WIDE, gamma, delta, seeding))
+    for B, V in ((3, 2051), (219, 2051)):    # one token per lane; vectors
+        rng = np.random.default_rng(5)
+        x = special_logits(rng, B, V, dtype)
+        prev = np.tile(np.array([0, -1, 2 ** 31 - 1], dtype=np.int32), B // 3)  # 0, 0xFFFFFFFF, ids >= V
+        for seeding in ("context", "self_salt"):
+            say(f"degenerate {dtype} {seeding} B={B} gamma={gamma} delta={delta}")
+            got = run_watermark(env, x, prev, WIDE, gamma, delta, seeding)
+            assert_logits_equal(got, oracle.watermark(x, prev, WIDE, gamma, delta, seeding))
 
 
 @pytest.mark.parametrize("seeding", ["context", "self_salt"])
@@ -317,16 +318,18 @@ BF16_DELTAS = [2.0 ** -149, -(2.0 ** -149), 1e-40, -3e-39, 1e-38, 1e-30, -1e-20,
                1 / 3, 2 / 3, math.pi, -math.e, math.sqrt(2)]
 
 
-@pytest.mark.parametrize("layout", ["vector", "unaligned"])
+@pytest.mark.parametrize("layout", ["vector", "unaligned", "token"])
 def test_bf16_rounding_every_pattern(env, layout):
     # Every bf16 bit pattern, all green (gamma = 1), one fp32 add and one rounding to
     # bf16 per element, for deltas from the smallest subnormal to 3e38: covers ties,
     # carries into the exponent, overflow to infinity, subnormal sums and NaN inputs.
     x = np.arange(1 << 16, dtype=np.uint32).astype(np.uint16).reshape(1, -1)
-    prev = np.array([7], dtype=np.int32)
+    if layout != "token":                    # eight rows: more than one token per lane takes
+        x = np.tile(x, (8, 1))
+    prev = np.full(x.shape[0], 7, dtype=np.int32)
     for delta in BF16_DELTAS:
         say(f"bf16 rounding {layout} delta={delta!r}")
-        if layout == "vector":
+        if layout != "unaligned":
             got = run_watermark(env, x, prev, KEY, 1.0, delta, "context")
         else:
             got = run_watermark(env, x, prev, KEY, 1.0, delta, "context", offset=1)

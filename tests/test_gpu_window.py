@@ -35,7 +35,7 @@ def run_detect_w(env, tok, width, key, gamma, seeding):
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("seeding", ["context", "self_salt"])
 @pytest.mark.parametrize("width", [1, 2, 4, 8])
-@pytest.mark.parametrize("B,V", [(1, 5), (3, 33), (4, 4097), (2, 32001)])
+@pytest.mark.parametrize("B,V", [(1, 5), (3, 33), (4, 4097), (2, 32001), (110, 4097)])
 def test_watermark_window(env, dtype, seeding, width, B, V):
     rng = np.random.default_rng(width * 1000 + B * 7 + V)
     x = special_logits(rng, B, V, dtype)
