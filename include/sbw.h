@@ -277,8 +277,9 @@ sbw_status_t sbw_watermark_candidates(void *logits, sbw_dtype_t dtype, int64_t B
  *                its contents on entry do not matter and are undefined on return.
  *                Calls that share a workspace must be ordered (same stream);
  *                concurrent calls race.
- * Enqueues two kernels on `stream` (the fused pass, then a per-row read-out) and no
- * memset, so the call can be captured in a HIP graph.
+ * Enqueues two kernels on `stream` (the fused pass, then a per-row read-out; one kernel, and
+ * no use of the workspace, for rows of a few hundred logits) and no memset, so the call can be
+ * captured in a HIP graph.
  */
 sbw_status_t sbw_watermark_argmax(const void *logits, sbw_dtype_t dtype, int64_t B, int64_t V,
                                   int64_t row_stride, const int32_t *context, int64_t width,
@@ -306,7 +307,8 @@ sbw_status_t sbw_watermark_argmax(const void *logits, sbw_dtype_t dtype, int64_t
  *   scores       device, [B] float, written (may be NULL): the winning score
  *                l'_v * inv_temperature + G_v.
  *   workspace    as for sbw_watermark_argmax, same size.
- * Enqueues two kernels on `stream` and no memset (graph-capturable).
+ * Enqueues one or two kernels on `stream`, as sbw_watermark_argmax does, and no memset
+ * (graph-capturable).
  */
 sbw_status_t sbw_watermark_sample(const void *logits, sbw_dtype_t dtype, int64_t B, int64_t V,
                                   int64_t row_stride, const int32_t *context, int64_t width,

@@ -15,7 +15,8 @@
 // argmax      greedy decoding of the watermarked logits without writing them: one
 //             read of each logit, a per-segment (value, index) partial, a read-out
 //             kernel per row.  Colours are drawn only for logits that can still
-//             reach the segment's maximum.
+//             reach the segment's maximum.  Rows of a few hundred tokens: every
+//             token scored, the winner stored, in one launch.
 // candidates  the watermark restricted to caller-given candidate ids per row (the
 //             top-k self-salt scheme): one workgroup per row.
 // green_mask  one lane per 32-token word of the bit set.
@@ -1293,6 +1294,62 @@ decode_vec_kernel(const T* __restrict__ logits, int64_t row_stride, uint32_t V, 
   }
 }
 
+// Decoding of short rows, which need no partials: kRowWaves waves score every token of a row,
+// at most kShortSteps a lane, and store the winner, in one launch.  Bound by a lane's chain
+// (window, colour, sampling two logarithms) in small launches, by VALU issue in large ones; the
+// segment pass spends its fixed part (bounds, queues, a read-out launch) on few tokens.  us,
+// segments / this: greedy fp32 1 x 37 4.5 / 2.2, 1000 x 513 6.6 / 4.1; sampling 5000 x 100 31.1 /
+// 5.4, 1000 x 1001 8.5 / 7.3.
+constexpr int kShortSteps = 4;
+template <typename T, int kSeeding, int kW, bool kSample, int kRowWaves>
+__global__ void __launch_bounds__(kThreads)
+decode_short_kernel(const T* __restrict__ logits, int64_t row_stride, uint32_t V, int64_t B,
+                    const int32_t* __restrict__ context, int width, uint64_t key, uint32_t tm1,
+                    int none_green, float delta, const uint64_t* __restrict__ seeds, float inv_t,
+                    int32_t* __restrict__ tokens, float* __restrict__ values, uint32_t vbase) {
+  constexpr int kWaves = kThreads / 64, kRows = kWaves / kRowWaves;
+  __shared__ uint64_t lds_key[kWaves], lds_part[kWaves];
+  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x / 64u));
+  const uint32_t t = threadIdx.x % (64u * kRowWaves);
+  for (int64_t row = static_cast<int64_t>(blockIdx.x) * kRows + wave / kRowWaves; row < B;
+       row += static_cast<int64_t>(gridDim.x) * kRows) {
+    const T* row_ptr = logits + row * row_stride;
+    T raw[kShortSteps];
+#pragma unroll
+    for (uint32_t n = 0; n < kShortSteps; ++n) {
+      const uint32_t c = t + n * 64u * kRowWaves;
+      if (c < V) raw[n] = row_ptr[c];
+    }
+    const RowSeed<kW> rs = row_seed<kSeeding, kW>(key, context + row * width, width);
+    const Score<kSample> sc{kSample ? seeds[row] : 0u, inv_t};
+    LaneBest best = lane_best_init();
+#pragma unroll
+    for (uint32_t n = 0; n < kShortSteps; ++n) {
+      const uint32_t c = t + n * 64u * kRowWaves;
+      if (c < V)
+        score_entry<T, kSeeding, kW, kSample>(best, vbase + c, raw_bits(raw[n]), rs, tm1, none_green, delta, sc);
+    }
+    uint64_t k = best.any ? arg_key(best.v, best.i) : 0u;
+    uint64_t p = pack_partial(best.v, best.i);
+    wave_argmax(k, p);
+    if constexpr (kRowWaves > 1) {
+      if (threadIdx.x % 64u == 0u) {
+        lds_key[wave] = k;
+        lds_part[wave] = p;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w)
+        if (lds_key[w] > k) { k = lds_key[w]; p = lds_part[w]; }
+      __syncthreads();   // the slots are written again for the next row
+    }
+    if (t == 0u) {
+      tokens[row] = static_cast<int32_t>(static_cast<uint32_t>(p));
+      if (values != nullptr) values[row] = __uint_as_float(static_cast<uint32_t>(p >> 32));
+    }
+  }
+}
+
 // Read-out: one wavefront per row loads the row's partials at once, reduces their
 // keys with shuffles, and lane 0 unpacks the winner.
 __global__ void __launch_bounds__(kThreads)
@@ -2047,6 +2104,14 @@ struct SampleArgs {
   float inv_t;
 };
 
+// The longest rows for the short kernel, and of launches of up to kShortCells logits: with
+// many longer rows the tokens that the segment pass leaves undrawn are worth more than its
+// fixed part (self-salt greedy fp32, 5000 x 513 14.3 us in segments, 13.4 here, x 1001 14.8 /
+// 17.5; 1000 x 1001 6.7 / 5.6).
+constexpr uint32_t kShortRow = 640, kShortRowFew = 1024;
+constexpr int64_t kShortCells = int64_t{1} << 20;
+static_assert(kShortRowFew <= kThreads * kShortSteps, "a workgroup holds a short row");
+
 template <typename T, int kSeeding, int kW, bool kSample>
 void launch_argmax(const void* logits, int64_t B, uint32_t V, int64_t row_stride,
                    const int32_t* context, int width, uint64_t key, uint32_t tm1, int none,
@@ -2054,6 +2119,21 @@ void launch_argmax(const void* logits, int64_t B, uint32_t V, int64_t row_stride
                    uint64_t* partials, hipStream_t stream) {
   const T* p = static_cast<const T*>(logits);
   const uint32_t rows = static_cast<uint32_t>(B < kMaxGridY ? B : kMaxGridY);
+  if (V <= kShortRow || (V <= kShortRowFew && B <= kShortCells / V)) {
+    auto launch_short = [&](auto row_waves) {
+      constexpr int kRowWaves = decltype(row_waves)::value;
+      constexpr int kRows = kThreads / 64 / kRowWaves;
+      hipLaunchKernelGGL((decode_short_kernel<T, kSeeding, kW, kSample, kRowWaves>),
+                         dim3(static_cast<uint32_t>(grid_for((B + kRows - 1) / kRows))), dim3(kThreads), 0,
+                         stream, p, row_stride, V, B, context, width, key, tm1, none, delta, sa.seeds,
+                         sa.inv_t, tokens, values, vbase);
+    };
+    // one wave a row where the rows fill the chip or one step holds them (1000 x 256 greedy 3.2
+    // us, 3.6 with four waves; 64 x 256 sampling 4.1 / 3.2)
+    if (V <= 64u || (V <= 64u * kShortSteps && B >= 512)) launch_short(std::integral_constant<int, 1>{});
+    else launch_short(std::integral_constant<int, kThreads / 64>{});
+    return;
+  }
   constexpr int kSub = decode_subs_for<T>(kSample);
   constexpr int kN = decode_vecs_for<T>(kSample) / kSub;
   constexpr int kNs = kN * kSub / 2;
