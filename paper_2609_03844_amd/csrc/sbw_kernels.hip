@@ -259,26 +259,30 @@ __device__ __forceinline__ uint16_t bias_elem(uint16_t l, float d, bool g) {
   return bias_bf16(l, d, g);
 }
 
-// The columns outside whole vectors (RowSplit), one lane a column, 16 rows a workgroup: the
-// workgroups of a launch's last `edge_y` grid rows take them, after the tiles'.  A path of its
-// own, so that the tiles' path keeps no registers for it (inside the tiles it cost 2-13 VGPRs
-// a lane and with them a wave per SIMD: bf16 self-salt 256 x 152064, width 4, 96 -> 106 us),
-// and only as many workgroups as have work: a column of one per row, most of them empty, cost
-// their dispatch (1000 x 2001 fp32, self-salt: 9.5 us, 6.6 so; 500 x 32001 bf16, 32.0, 28.4).
-// In front of the tiles they delay these (48 x 128259 bf16, self-salt: 14.3 us, 13.3 behind).
-__device__ __forceinline__ uint32_t tile_rows(uint32_t edge_y) { return gridDim.y - edge_y; }
+// The columns outside whole vectors (RowSplit), one lane a column, 16 rows a workgroup, in
+// grid rows of their own.  A path of its own, so that the tiles' path keeps no registers for
+// it (inside the tiles it cost 2-13 VGPRs a lane and with them a wave per SIMD: bf16 self-salt
+// 256 x 152064, width 4, 96 -> 106 us), and only as many workgroups as have work: a column of
+// one per row, most of them empty, cost their dispatch (1000 x 2001 fp32, self-salt: 9.5 us,
+// 6.6 so; 500 x 32001 bf16, 32.0, 28.4).  They are a launch's grid rows from `slots` on, behind
+// the tiles, which they delay in front (48 x 128259 bf16, self-salt: 14.3 us, 13.3 behind) and
+// between (16.7); only context launches of many rows, bound by memory, spread them between the
+// tiles, every 2^shift-th grid row (353 x 30079 bf16: 9.9 us behind, 9.5 spread; 500 x 32001
+// 13.4 / 12.8; but 48 x 128259 6.5 / 6.75, 200 x 50257 9.0 / 9.1).
+constexpr int64_t kSpreadRows = 300;
 constexpr uint32_t kEdgeRows = 16;
 static_assert(kThreads / kEdgeRows >= 14, "a row has at most 7 + 7 such columns");
 template <typename T, int kSeeding, int kW, uint32_t kPer>
 __device__ __forceinline__ void watermark_edges(T* logits, int64_t row_stride, const RowSplit& sp,
                                                 int64_t B, const int32_t* context, int width,
                                                 uint64_t key, uint32_t tm1, float delta,
-                                                uint32_t vbase, uint32_t edge_y) {
-  const int64_t slot = static_cast<int64_t>(blockIdx.y - tile_rows(edge_y)) * gridDim.x + blockIdx.x;
+                                                uint32_t vbase, uint32_t edge_row,
+                                                uint32_t edge_rows) {
+  const int64_t slot = static_cast<int64_t>(edge_row) * gridDim.x + blockIdx.x;
   const uint32_t e = threadIdx.x % (kThreads / kEdgeRows);
   if (e >= sp.edges()) return;
   for (int64_t row = slot * kEdgeRows + threadIdx.x / (kThreads / kEdgeRows); row < B;
-       row += static_cast<int64_t>(edge_y) * gridDim.x * kEdgeRows) {
+       row += static_cast<int64_t>(edge_rows) * gridDim.x * kEdgeRows) {
     // the logit is on its way while the window is read and the colour drawn
     T* p = logits + row * row_stride + sp.edge<kPer>(e);
     const T l = *p;
@@ -288,36 +292,39 @@ __device__ __forceinline__ void watermark_edges(T* logits, int64_t row_stride, c
 }
 
 // Context-seeded watermark.  Grid: x = tile of kThreads * kU vectors within a row, y = row
-// (grid-stride over rows beyond 65535), then edge_y rows for the edge columns.  Each lane issues its logits load before reading the row's window, so the
-// scalar loads of the window overlap the HBM stream.  With xcd_rows (one row per y,
-// B a multiple of 8) the workgroups are renumbered so that each of the 8 XCDs, which
-// take workgroups in turn, streams whole rows: workgroup n goes to row
-// 8 * (n / 8 / tiles) + n % 8, tile n / 8 % tiles.
-template <typename T, int kU, int kW>
+// (grid-stride over rows beyond the `slots` of the tiles), then grid rows for the edge columns;
+// kSpread: every 2^slots-th grid row.
+// Each lane issues its logits load before reading the row's window, so the scalar loads of
+// the window overlap the HBM stream.  With xcd_rows (one row per y, B a multiple of 8) the
+// workgroups are renumbered so that each of the 8 XCDs, which take workgroups in turn,
+// streams whole rows: workgroup n goes to row 8 * (n / 8 / tiles) + n % 8, tile n / 8 % tiles.
+template <typename T, int kU, int kW, bool kSpread>
 __global__ void __launch_bounds__(kThreads)
 watermark_vec_kernel(T* __restrict__ logits, int64_t row_stride, uint32_t V, int64_t B,
                      const int32_t* __restrict__ context, int width, uint64_t key, uint32_t tm1,
-                     float delta, uint32_t vbase, uint32_t xcd_rows, uint32_t edge_y) {
+                     float delta, uint32_t vbase, uint32_t xcd_rows, uint32_t slots) {
   using VecT = typename VecOf<T>::Value;
   using MemT = typename VecOf<T>::Memory;
   constexpr uint32_t kPer = 16u / sizeof(T);  // elements per 16-byte vector
   const RowSplit sp = row_split<kPer>(V, vbase);
   const uint32_t full = sp.full;
   const uint32_t jbase = sp.id;
-  if (blockIdx.y >= tile_rows(edge_y)) {
+  if (kSpread ? ((blockIdx.y + 1u) & ((1u << slots) - 1u)) == 0u : blockIdx.y >= slots) {
     watermark_edges<T, kContext, kW, kPer>(logits, row_stride, sp, B, context, width, key, tm1, delta, vbase,
-                                           edge_y);
+                                           kSpread ? blockIdx.y >> slots : blockIdx.y - slots,
+                                           kSpread ? gridDim.y >> slots : gridDim.y - slots);
     return;
   }
+  const uint32_t y = kSpread ? blockIdx.y - (blockIdx.y >> slots) : blockIdx.y;   // among the tiles' rows
   uint32_t first = blockIdx.x * (kThreads * kU);
-  int64_t row0 = blockIdx.y;
+  int64_t row0 = y;
   if (xcd_rows != 0u) {
-    const uint32_t n = blockIdx.y * gridDim.x + blockIdx.x;
+    const uint32_t n = y * gridDim.x + blockIdx.x;
     const uint32_t q = n >> 3;
     row0 = static_cast<int64_t>(q / gridDim.x) * 8 + (n & 7u);
     first = (q % gridDim.x) * (kThreads * kU);
   }
-  for (int64_t row = row0; row < B; row += tile_rows(edge_y)) {
+  for (int64_t row = row0; row < B; row += kSpread ? gridDim.y - (gridDim.y >> slots) : slots) {
     MemT* vec = reinterpret_cast<MemT*>(logits + row * row_stride + sp.head);
     const int32_t* window = context + row * width;
     VecT buf[kU];
@@ -390,8 +397,8 @@ __device__ __forceinline__ u32x2 bias_quad(u32x2 l, const uint32_t (&x)[4], uint
                bias_bf16x2(l.y, delta, is_green(x[2], tm1), is_green(x[3], tm1))};
 }
 
-// Grid: x = tile of kThreads * kU quads of a row, y = a slot that takes the rows y, y + the
-// number of slots, ...; then edge_y rows for the edge columns.  The candidate terms depend on the columns only, so a workgroup
+// Grid: x = tile of kThreads * kU quads of a row, y = a slot that takes the rows y, y + slots,
+// ...; then grid rows for the edge columns.  The candidate terms depend on the columns only, so a workgroup
 // computes them once, while its first row's loads are in flight, and uses them for every
 // row it takes.  Bound by VALU issue: at width 4 a logit costs about 75 instructions, 51
 // of them its Philox block.  The window is a template parameter, so the minimum is a
@@ -405,7 +412,7 @@ template <typename T, int kU, int kW>
 __global__ void __launch_bounds__(kThreads)
 watermark_ss_rows_kernel(T* __restrict__ logits, int64_t row_stride, uint32_t V, int64_t B,
                          const int32_t* __restrict__ context, uint64_t key, uint32_t tm1, float delta,
-                         uint32_t vbase, uint32_t edge_y) {
+                         uint32_t vbase, uint32_t slots) {
   using QuadT = typename QuadOf<T>::Value;
   using MemT = typename QuadOf<T>::Memory;
   const RowSplit sp = row_split<4>(V, vbase);
@@ -413,13 +420,14 @@ watermark_ss_rows_kernel(T* __restrict__ logits, int64_t row_stride, uint32_t V,
   const uint32_t first = blockIdx.x * (kThreads * kU);
   const uint32_t id_first = first + sp.id;   // the tile's first quad counted in token ids
   const bool whole = first + kThreads * kU <= full;
-  if (blockIdx.y >= tile_rows(edge_y)) {
-    watermark_edges<T, kSelfSalt, kW, 4>(logits, row_stride, sp, B, context, kW, key, tm1, delta, vbase, edge_y);
+  if (blockIdx.y >= slots) {
+    watermark_edges<T, kSelfSalt, kW, 4>(logits, row_stride, sp, B, context, kW, key, tm1, delta, vbase,
+                                         blockIdx.y - slots, gridDim.y - slots);
     return;
   }
   CandTerm ct[kU][4];
   bool have_terms = false;
-  for (int64_t row = blockIdx.y; row < B; row += tile_rows(edge_y)) {
+  for (int64_t row = blockIdx.y; row < B; row += slots) {
     MemT* quads = reinterpret_cast<MemT*>(logits + row * row_stride + sp.head);
     QuadT buf[kU];
 #pragma unroll
@@ -624,7 +632,7 @@ __device__ __forceinline__ void slab_positions(SlabLds<kRows, kPer>& s, int rows
 }
 
 // Grid: x = tile of kThreads vectors (4 waves of 256 vectors), y = a slot taking the
-// slabs y, y + the number of slots, ... of kRows rows; then edge_y rows for the edges.  T: float (4 tokens a vector) or bf16
+// slabs y, y + slots, ... of kRows rows; then grid rows for the edge columns.  T: float (4 tokens a vector) or bf16
 // bits (8).  Rows of whole vectors have an instantiation of their own (kEdges false): the
 // path of the other columns in front of the tiles cost every wave its test and 0.8 %
 // (256 x 152064 fp32: 64.9 us without it, 65.5 with; 1024: 237.1 / 238.7).
@@ -632,7 +640,7 @@ template <typename T, int kRows, bool kEdges>
 __global__ void __launch_bounds__(kThreads)
 watermark_ss_slab_kernel(T* __restrict__ logits, int64_t row_stride, uint32_t V, int64_t B,
                          const int32_t* __restrict__ context, uint64_t key, uint32_t tm1,
-                         float delta, uint32_t vbase, uint32_t edge_y) {
+                         float delta, uint32_t vbase, uint32_t slots) {
   using VecT = typename VecOf<T>::Value;
   using MemT = typename VecOf<T>::Memory;
   constexpr int kPer = 16 / sizeof(T);  // tokens a vector
@@ -643,11 +651,11 @@ watermark_ss_slab_kernel(T* __restrict__ logits, int64_t row_stride, uint32_t V,
   SlabLds<kRows, kPer>& s = lds[wave];
   const RowSplit sp = kEdges ? row_split<kPer>(V, vbase) : RowSplit{0u, V / kPer, 0u, vbase / kPer};
   const uint32_t full = sp.full;
-  if (kEdges && blockIdx.y >= tile_rows(edge_y)) {
-    watermark_edges<T, kSelfSalt, 1, kPer>(logits, row_stride, sp, B, context, 1, key, tm1, delta, vbase, edge_y);
+  if (kEdges && blockIdx.y >= slots) {
+    watermark_edges<T, kSelfSalt, 1, kPer>(logits, row_stride, sp, B, context, 1, key, tm1, delta, vbase,
+                                           blockIdx.y - slots, gridDim.y - slots);
     return;
   }
-  const uint32_t slots = kEdges ? tile_rows(edge_y) : gridDim.y;
   const uint32_t j0 = blockIdx.x * kThreads + wave * 64u;  // the wave's first vector
   const uint32_t j = j0 + lane;
   const bool active = j < full;
@@ -1957,15 +1965,15 @@ void launch_watermark(void* logits, int64_t B, uint32_t V, int64_t row_stride,
   constexpr uint32_t kPer = 16u / sizeof(T);
   const RowSplit sp = row_split<kPer>(V, vbase);
   const uint64_t vectors = sp.full;
-  // grid rows for the edge columns, and the rows of the grid with `slots` of them for the tiles
+  // grid rows for the edge columns, and those that `most` rows of tiles take beside them
   auto edge_rows = [&](const RowSplit& r, uint32_t tiles) -> uint32_t {
     if (r.head + r.tail == 0u) return 0u;
     const int64_t groups = (B + kEdgeRows - 1) / kEdgeRows;
     const int64_t y = (groups + tiles - 1) / tiles;
     return static_cast<uint32_t>(y < kMaxEdgeY ? y : kMaxEdgeY);
   };
-  auto grid_y = [&](int64_t slots, uint32_t edge_y) {
-    return static_cast<uint32_t>(slots < kMaxGridY - edge_y ? slots : kMaxGridY - edge_y) + edge_y;
+  auto slots_of = [&](int64_t most, uint32_t edge_y) {
+    return static_cast<uint32_t>(most < kMaxGridY - edge_y ? most : kMaxGridY - edge_y);
   };
   if constexpr (kSeeding == kSelfSalt) {
     if constexpr (kW == 1) {
@@ -1977,13 +1985,14 @@ void launch_watermark(void* logits, int64_t B, uint32_t V, int64_t row_stride,
                               : sizeof(T) == 2 ? SBW_SLAB_BF16_MIN_GROUPS : SBW_SLAB_MIN_GROUPS;
         if (static_cast<int64_t>(tiles1) * slabs < least) return false;
         const uint32_t edge_y = edge_rows(sp, tiles1);
-        const dim3 grid(tiles1, grid_y(slabs, edge_y));
+        const uint32_t slots = slots_of(slabs, edge_y);
+        const dim3 grid(tiles1, slots + edge_y);
         if (edge_y != 0u)
           hipLaunchKernelGGL((watermark_ss_slab_kernel<T, kRows, true>), grid, dim3(kThreads), 0, stream, p,
-                             row_stride, V, B, context, key, tm1, delta, vbase, edge_y);
+                             row_stride, V, B, context, key, tm1, delta, vbase, slots);
         else
           hipLaunchKernelGGL((watermark_ss_slab_kernel<T, kRows, false>), grid, dim3(kThreads), 0, stream, p,
-                             row_stride, V, B, context, key, tm1, delta, vbase, 0u);
+                             row_stride, V, B, context, key, tm1, delta, vbase, slots);
         return true;
       };
       if (launch_slab(std::integral_constant<int, 12>{})) return;
@@ -1996,15 +2005,15 @@ void launch_watermark(void* logits, int64_t B, uint32_t V, int64_t row_stride,
     const uint32_t tiles2 = (quads.full + 2 * kThreads - 1) / (2 * kThreads);
     if (tiles2 * B < kTwoQuadMinGroups) {
       const uint32_t tiles = (quads.full + kThreads - 1) / kThreads;
-      const uint32_t edge_y = edge_rows(quads, tiles);
-      hipLaunchKernelGGL((watermark_ss_rows_kernel<T, 1, kW>), dim3(tiles, grid_y(B, edge_y)), dim3(kThreads),
-                         0, stream, p, row_stride, V, B, context, key, tm1, delta, vbase, edge_y);
+      const uint32_t edge_y = edge_rows(quads, tiles), slots = slots_of(B, edge_y);
+      hipLaunchKernelGGL((watermark_ss_rows_kernel<T, 1, kW>), dim3(tiles, slots + edge_y), dim3(kThreads),
+                         0, stream, p, row_stride, V, B, context, key, tm1, delta, vbase, slots);
       return;
     }
-    const int64_t slots = (B + rows_per_slot(tiles2, B) - 1) / rows_per_slot(tiles2, B);
     const uint32_t edge_y = edge_rows(quads, tiles2);
-    hipLaunchKernelGGL((watermark_ss_rows_kernel<T, 2, kW>), dim3(tiles2, grid_y(slots, edge_y)),
-                       dim3(kThreads), 0, stream, p, row_stride, V, B, context, key, tm1, delta, vbase, edge_y);
+    const uint32_t slots = slots_of((B + rows_per_slot(tiles2, B) - 1) / rows_per_slot(tiles2, B), edge_y);
+    hipLaunchKernelGGL((watermark_ss_rows_kernel<T, 2, kW>), dim3(tiles2, slots + edge_y), dim3(kThreads), 0,
+                       stream, p, row_stride, V, B, context, key, tm1, delta, vbase, slots);
   } else {
     // Two vectors in flight per lane measured best (~80 % of HBM peak; one: ~75 %).
     constexpr int kU = sizeof(T) == 4 ? SBW_CONTEXT_UNROLL : SBW_CONTEXT_UNROLL_BF16;
@@ -2012,15 +2021,28 @@ void launch_watermark(void* logits, int64_t B, uint32_t V, int64_t row_stride,
     // whole rows per XCD for large launches (one launch row per grid row, workgroup
     // numbers below 2^32)
     const uint32_t edge_y = edge_rows(sp, tiles);
+    const bool spread = edge_y != 0u && B >= kSpreadRows;
+    // spread: the rarest grid rows that are enough for the edges, rows / (2^shift - 1) of them
+    // (every second one at most; each takes more rows in turn where that is too few)
+    uint32_t shift = 1u;
+    while (spread && rows / ((uint64_t{2} << shift) - 1) >= edge_y) ++shift;
+    const uint64_t every = (uint64_t{1} << shift) - 1;
+    const uint64_t grid_rows = spread ? rows + (rows + every - 1) / every : uint64_t{rows} + edge_y;
     const uint32_t xcd_rows =
-        B >= SBW_XCD_ROWS_MIN && B % 8 == 0 && B <= kMaxGridY - edge_y &&
+        B >= SBW_XCD_ROWS_MIN && B % 8 == 0 && grid_rows <= kMaxGridY &&
                 B * static_cast<int64_t>(V) * static_cast<int64_t>(sizeof(T)) >= SBW_XCD_ROWS_MIN_BYTES &&
-                uint64_t{tiles} * static_cast<uint64_t>(B) < (uint64_t{1} << 32)
+                uint64_t{tiles} * grid_rows < (uint64_t{1} << 32)
             ? 1u
             : 0u;
-    hipLaunchKernelGGL((watermark_vec_kernel<T, kU, kW>), dim3(tiles, grid_y(B, edge_y)),
-                       dim3(kThreads), 0, stream, p, row_stride, V, B, context, width, key, tm1,
-                       delta, vbase, xcd_rows, edge_y);
+    const uint32_t slots = slots_of(B, edge_y);
+    const dim3 grid(tiles, spread ? static_cast<uint32_t>(grid_rows < kMaxGridY ? grid_rows : kMaxGridY)
+                                  : slots + edge_y);
+    if (spread)
+      hipLaunchKernelGGL((watermark_vec_kernel<T, kU, kW, true>), grid, dim3(kThreads), 0, stream, p, row_stride,
+                         V, B, context, width, key, tm1, delta, vbase, xcd_rows, shift);
+    else
+      hipLaunchKernelGGL((watermark_vec_kernel<T, kU, kW, false>), grid, dim3(kThreads), 0, stream, p, row_stride,
+                         V, B, context, width, key, tm1, delta, vbase, xcd_rows, slots);
   }
 }
 

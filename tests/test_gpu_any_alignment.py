@@ -112,6 +112,14 @@ def test_context_whole_rows_per_xcd_with_edges(env, dtype):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("B,n", [(299, 2051), (300, 2051), (301, 5003), (3000, 301), (4999, 517), (40003, 270)])
+def test_context_edges_behind_and_between_the_tiles(env, dtype, B, n):
+    """From 300 rows the edge columns' grid rows are spread between the tiles': one of them and
+    many, each with one and with many tiles, and rows that are not a multiple of their distance."""
+    check(env, dtype, "context", 2, B, 3, n, offset=1, pad=1)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("sample", [False, True])
 @pytest.mark.parametrize("B,start,n,pad", [(3, 1, 1, 0), (5, 3, 4, 1), (4, 5, 15, 0), (3, 7, 4096, 3),
                                            (2, 2, 12290, 1), (200, 1003, 40969, 2)])
