@@ -408,7 +408,10 @@ __device__ __forceinline__ u32x2 bias_quad(u32x2 l, const uint32_t (&x)[4], uint
 // per lane, 8 waves per SIMD instead of 4 (96.8 -> 77.9 us at 256 x 152064, width 4).
 // Several rows at once per workgroup (their loads and draws side by side) measured slower
 // than one after another at every size.
-template <typename T, int kU, int kW>
+// Rows of whole quads have an instantiation of their own: beside the edges' code the
+// compiler gives the main path more registers and a worse order (129 x 19648, width 4, us:
+// bf16 9.36 with it, 9.12 without; fp32 9.40, 9.26).
+template <typename T, int kU, int kW, bool kEdges>
 __global__ void __launch_bounds__(kThreads)
 watermark_ss_rows_kernel(T* __restrict__ logits, int64_t row_stride, uint32_t V, int64_t B,
                          const int32_t* __restrict__ context, uint64_t key, uint32_t tm1, float delta,
@@ -420,7 +423,7 @@ watermark_ss_rows_kernel(T* __restrict__ logits, int64_t row_stride, uint32_t V,
   const uint32_t first = blockIdx.x * (kThreads * kU);
   const uint32_t id_first = first + sp.id;   // the tile's first quad counted in token ids
   const bool whole = first + kThreads * kU <= full;
-  if (blockIdx.y >= slots) {
+  if (kEdges && blockIdx.y >= slots) {
     watermark_edges<T, kSelfSalt, kW, 4>(logits, row_stride, sp, B, context, kW, key, tm1, delta, vbase,
                                          blockIdx.y - slots, gridDim.y - slots);
     return;
@@ -2006,14 +2009,22 @@ void launch_watermark(void* logits, int64_t B, uint32_t V, int64_t row_stride,
     if (tiles2 * B < kTwoQuadMinGroups) {
       const uint32_t tiles = (quads.full + kThreads - 1) / kThreads;
       const uint32_t edge_y = edge_rows(quads, tiles), slots = slots_of(B, edge_y);
-      hipLaunchKernelGGL((watermark_ss_rows_kernel<T, 1, kW>), dim3(tiles, slots + edge_y), dim3(kThreads),
-                         0, stream, p, row_stride, V, B, context, key, tm1, delta, vbase, slots);
+      if (edge_y != 0u)
+        hipLaunchKernelGGL((watermark_ss_rows_kernel<T, 1, kW, true>), dim3(tiles, slots + edge_y), dim3(kThreads),
+                           0, stream, p, row_stride, V, B, context, key, tm1, delta, vbase, slots);
+      else
+        hipLaunchKernelGGL((watermark_ss_rows_kernel<T, 1, kW, false>), dim3(tiles, slots + edge_y), dim3(kThreads),
+                           0, stream, p, row_stride, V, B, context, key, tm1, delta, vbase, slots);
       return;
     }
     const uint32_t edge_y = edge_rows(quads, tiles2);
     const uint32_t slots = slots_of((B + rows_per_slot(tiles2, B) - 1) / rows_per_slot(tiles2, B), edge_y);
-    hipLaunchKernelGGL((watermark_ss_rows_kernel<T, 2, kW>), dim3(tiles2, slots + edge_y), dim3(kThreads), 0,
-                       stream, p, row_stride, V, B, context, key, tm1, delta, vbase, slots);
+    if (edge_y != 0u)
+      hipLaunchKernelGGL((watermark_ss_rows_kernel<T, 2, kW, true>), dim3(tiles2, slots + edge_y), dim3(kThreads),
+                         0, stream, p, row_stride, V, B, context, key, tm1, delta, vbase, slots);
+    else
+      hipLaunchKernelGGL((watermark_ss_rows_kernel<T, 2, kW, false>), dim3(tiles2, slots + edge_y), dim3(kThreads),
+                         0, stream, p, row_stride, V, B, context, key, tm1, delta, vbase, slots);
   } else {
     // Two vectors in flight per lane measured best (~80 % of HBM peak; one: ~75 %).
     constexpr int kU = sizeof(T) == 4 ? SBW_CONTEXT_UNROLL : SBW_CONTEXT_UNROLL_BF16;
