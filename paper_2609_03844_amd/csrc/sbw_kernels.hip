@@ -408,9 +408,9 @@ __device__ __forceinline__ u32x2 bias_quad(u32x2 l, const uint32_t (&x)[4], uint
 // per lane, 8 waves per SIMD instead of 4 (96.8 -> 77.9 us at 256 x 152064, width 4).
 // Several rows at once per workgroup (their loads and draws side by side) measured slower
 // than one after another at every size.
-// Rows of whole quads have an instantiation of their own: beside the edges' code the
-// compiler gives the main path more registers and a worse order (129 x 19648, width 4, us:
-// bf16 9.36 with it, 9.12 without; fp32 9.40, 9.26).
+// Rows of whole quads have an instantiation of their own: beside the edges' code the main
+// path runs slower, in as many registers (129 x 19648, width 4, us: bf16 9.36 with it, 9.12
+// without; fp32 9.40, 9.26).
 template <typename T, int kU, int kW, bool kEdges>
 __global__ void __launch_bounds__(kThreads)
 watermark_ss_rows_kernel(T* __restrict__ logits, int64_t row_stride, uint32_t V, int64_t B,
